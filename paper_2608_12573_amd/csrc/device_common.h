@@ -311,29 +311,25 @@ __device__ __forceinline__ void rank_bin_search(const uint32_t* hist, uint32_t n
   const int lane = threadIdx.x & (kWave - 1);
   if (nb >= static_cast<uint32_t>(4 * kWave)) {
     // lane L owns bins [nb - (L+1)*per, nb - L*per); lane 0 the highest
-    const uint32_t per = nb / kWave;  // a multiple of 4
-    const uint32_t base = nb - (lane + 1) * per;
+    const uint32_t per = nb / kWave;  // a multiple of 4, at most 64
     uint32_t loc = 0;
+#pragma unroll 4
     for (uint32_t q = 0; q < per; q += 4) {
-      const uint4 v4 = *reinterpret_cast<const uint4*>(&hist[base + q]);
+      const uint4 v4 = *reinterpret_cast<const uint4*>(&hist[nb - (lane + 1) * per + q]);
       loc += v4.x + v4.y + v4.z + v4.w;
     }
-    uint32_t run = wave_incl_sum(loc) - loc;
-    if (run < krem && krem <= run + loc) {
-      // the rank falls in this lane's bins: walk them from the top
-      for (int q = static_cast<int>(per) - 4; q >= 0; q -= 4) {
-        const uint4 v4 = *reinterpret_cast<const uint4*>(&hist[base + q]);
-        const uint32_t c4[4] = {v4.x, v4.y, v4.z, v4.w};
-#pragma unroll
-        for (int j = 3; j >= 0; --j) {
-          if (run < krem && krem <= run + c4[j]) {
-            sh.found[0] = base + q + j;
-            sh.found[1] = run;
-            sh.found[2] = c4[j];
-          }
-          run += c4[j];
-        }
-      }
+    const uint32_t incl = wave_incl_sum(loc);
+    // the lane whose bins hold the rank, then its bins one per lane, highest
+    // first (a second scan, where that lane alone would walk them in turn)
+    const int own = __ffsll(static_cast<unsigned long long>(__ballot(krem <= incl))) - 1;
+    const uint32_t above = __builtin_amdgcn_readlane(incl - loc, own);
+    const uint32_t top = nb - own * per - 1;
+    const uint32_t c = static_cast<uint32_t>(lane) < per ? hist[top - lane] : 0u;
+    const uint32_t run = above + wave_incl_sum(c) - c;
+    if (run < krem && krem <= run + c) {
+      sh.found[0] = top - lane;
+      sh.found[1] = run;
+      sh.found[2] = c;
     }
   } else {
     // at most 128 bins: lane L owns descending ranks [L*per, (L+1)*per)
@@ -500,55 +496,95 @@ __device__ __forceinline__ uint32_t tau_pair_index(Draws draws, uint32_t tau, ui
   return ~res.kth;
 }
 
-// Top-t of up to 64*E keys held by one wave (E per lane, `valid` bits mark
-// which of a lane's slots hold keys): t rounds of a wave-wide max; the lowest
-// lane holding the maximum gives up one copy and stores it to out[round]
-// (out may be null).  Returns got = min(t, number of keys); `last` receives
-// the got-th largest key in every lane.  v is left as it was.
+// The kk-th largest (1-based, with multiplicity) of the keys the threads of a
+// block hold in registers (E per thread, `valid` bits mark which): .x the
+// key, .y the number of keys above it.  Requires 1 <= kk <= #keys.
+// `hist` is 2^DIGIT words of LDS (16-byte aligned), `list` kListRankMax
+// words, `red` 2*BS/64 + 2 words; all may be reused once it returns (it ends
+// with a barrier).
 //
-// Each lane first sorts a copy of its keys in descending order (empty slots
-// as 0, the lowest key: a lane's first n slots then hold its n keys, since a
-// key of 0 and an empty slot are alike), so a round reads every lane's head
-// and the lane that gives it up shifts its copy by one.
-template <int E>
-__device__ __forceinline__ uint32_t wave_top_t(const uint32_t (&v)[E], uint32_t valid, uint32_t t,
-                                               uint32_t* out, uint32_t& last) {
-  const int lane = threadIdx.x & (kWave - 1);
-  uint32_t s[E];
-  uint32_t n = 0;
+// The keys' distances from their minimum are histogrammed by their leading
+// DIGIT bits, so that the bins resolve the range the keys span and not the
+// whole key range; the bin of rank kk then holds few keys, which are ranked
+// by counting.  A bin that holds more is split again, down to one key wide.
+// What bounds it is latency: six barriers and a few hundred LDS reads,
+// whatever kk.  Taking a wave-wide maximum per rank instead (in every wave,
+// then over the waves' lists) cost about 420 cycles per rank, twice: 15800
+// cycles for the 22nd of 382 keys on 256 threads, against 6000 here.
+template <int BS, int E, int DIGIT>
+__device__ __forceinline__ uint2 block_kth_regs(const uint32_t (&kv)[E], uint32_t valid, uint32_t kk,
+                                                uint32_t* hist, uint32_t* list, uint32_t* red,
+                                                SelectScratch& sc) {
+  constexpr int NW = BS / kWave;
+  constexpr uint32_t NB = 1u << DIGIT;
+  const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
+  uint32_t mx = 0, nmn = 0;  // largest key, complement of the smallest
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const bool in = (valid >> e) & 1u;
-    s[e] = in ? v[e] : 0u;
-    n += in ? 1u : 0u;
+    mx = max(mx, in ? kv[e] : 0u);
+    nmn = max(nmn, in ? ~kv[e] : 0u);
   }
-  // odd-even transposition sort, descending (E rounds sort E values)
-#pragma unroll
-  for (int r = 0; r < E; ++r)
-#pragma unroll
-    for (int j = r & 1; j + 1 < E; j += 2) {
-      const uint32_t hi = max(s[j], s[j + 1]), lo = min(s[j], s[j + 1]);
-      s[j] = hi;
-      s[j + 1] = lo;
-    }
-  uint32_t got = 0;
-  for (; got < t; ++got) {
-    const bool have = n > 0;
-    if (__ballot(have) == 0) break;
-    const uint32_t wm = wave_max_u32(have ? s[0] : 0u);
-    last = wm;
-    // lanes whose head equals the wave maximum; the lowest one gives it up
-    const uint64_t holders = __ballot(have && s[0] == wm);
-    const int owner = __ffsll(static_cast<unsigned long long>(holders)) - 1;
-    if (lane == owner) {
-#pragma unroll
-      for (int e = 0; e + 1 < E; ++e) s[e] = s[e + 1];
-      s[E - 1] = 0;
-      --n;
-      if (out) out[got] = wm;
-    }
+  mx = wave_max_u32(mx);
+  nmn = wave_max_u32(nmn);
+  if (lane == 0) {
+    red[w] = mx;
+    red[NW + w] = nmn;
   }
-  return got;
+  if (tid == 0) red[2 * NW] = 0;  // entries of `list`
+  for (uint32_t b = tid; b < NB; b += BS) hist[b] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    mx = max(mx, red[i]);
+    nmn = max(nmn, red[NW + i]);
+  }
+  uint32_t base = ~nmn, krem = kk, above = 0;
+  int wb = mx == base ? 0 : 32 - __clz(mx - base);  // the window is [base, base + 2^wb)
+  while (true) {
+    const int shift = wb > DIGIT ? wb - DIGIT : 0;
+    const uint32_t span = wb >= 32 ? 0xFFFFFFFFu : (1u << wb) - 1u;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const uint32_t d = kv[e] - base;  // (keys below base wrap past the window or are tested by it)
+      hist_add(hist, d >> shift, ((valid >> e) & 1u) && kv[e] >= base && d <= span);
+    }
+    __syncthreads();
+    if (w == 0) rank_bin_search(hist, NB, krem, sc);
+    __syncthreads();
+    const uint32_t bin = sc.found[0], eq = sc.found[2];
+    above += sc.found[1];
+    krem -= sc.found[1];
+    base += bin << shift;
+    wb = shift;
+    if (shift == 0) break;  // one key wide
+    if (eq <= kListRankMax) {
+      uint32_t m = 0;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        m |= (((valid >> e) & 1u) && kv[e] >= base && ((kv[e] - base) >> shift) == 0 ? 1u : 0u) << e;
+      const uint32_t c = static_cast<uint32_t>(__popc(m)), incl = wave_incl_sum(c);
+      const uint32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
+      if (tot) {
+        uint32_t slot = 0;
+        if (lane == 0) slot = atomicAdd(&red[2 * NW], tot);
+        slot = __builtin_amdgcn_readlane(slot, 0) + incl - c;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+          if ((m >> e) & 1u) list[slot++] = kv[e];
+      }
+      __syncthreads();
+      list_kth<BS>(list, eq, krem, sc.found);
+      __syncthreads();
+      base = sc.found[0];
+      above += sc.found[1];
+      break;
+    }
+    for (uint32_t b = tid; b < NB; b += BS) hist[b] = 0;
+    __syncthreads();
+  }
+  __syncthreads();
+  return uint2{base, above};
 }
 
 // Number of leading bits shared by every value in [lo, hi] (lo <= hi),

@@ -28,6 +28,13 @@ struct FilterArgs {
   CallState* st;
   const uint32_t* union_keys;  // sample union to select tau from, or null: tau in st
   uint32_t union_n, t;
+  // capped sample lists: the n_cut blocks' cut keys and all n_all sample
+  // keys, as in k_select_tau; otherwise all_keys is null and cut any
+  // readable word (n_cut = 1)
+  const uint32_t* cut;
+  uint32_t n_cut;
+  const uint32_t* all_keys;
+  uint32_t n_all;
   uint32_t *seg_cnt, *seg_key, *seg_idx, *blk_max;
   uint32_t* fhist;             // refinement histogram (or null), zero on entry
 };
@@ -41,13 +48,14 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
   constexpr int EPV = Elem<DT>::EPV;
   constexpr int ES = Elem<DT>::ES;
   __shared__ uint32_t s_skey[kStage], s_sidx[kStage];
-  // the waves' top-t lists while tau is chosen, then the block's log-bin
+  // the histogram and list of the select of tau, then the block's log-bin
   // histogram of its survivors
   __shared__ __align__(16) uint32_t s_pool[kLogBins];
-  static_assert(kFiltBS / kWave * kWaveTopMax <= kLogBins, "tau lists");
-  uint32_t* const s_lists = s_pool;
-  __shared__ uint32_t s_found[kFiltBS / kWave];
-  __shared__ uint32_t s_cnt, s_tau, s_base;
+  constexpr int kTauDigit = 10;
+  static_assert((1u << kTauDigit) + kListRankMax <= kLogBins, "select of tau");
+  __shared__ uint32_t s_red[2 * (kFiltBS / kWave) + 2];
+  __shared__ SelectScratch s_sc;
+  __shared__ uint32_t s_cnt, s_base;
   __shared__ uint32_t s_wmax[kFiltBS / kWave];
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), b = blockIdx.x;
   const uint32_t seg = b & (kSegs - 1);
@@ -65,18 +73,16 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
   const uint32_t vend = a.nvec;
   const uint32_t vstride = gridDim.x * kTile;
   constexpr int E = kFiltTauMax / kFiltBS;
-  const bool one_wave = a.union_n <= kWave * kFiltTauWave;
   uint32_t uk[E];
-  uint32_t valid = 0;
+  uint32_t valid = 0, cutv = 0;
   if (a.union_n) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      // one wave: lane + 64 e for e < kFiltTauWave; four waves: tid + 256 e
-      const uint32_t i = one_wave ? lane + kWave * e : tid + kFiltBS * e;
-      const bool in = (one_wave ? (tid < kWave && e < static_cast<int>(kFiltTauWave)) : true) && i < a.union_n;
-      uk[e] = in ? a.union_keys[i] : 0u;
-      if (in) valid |= 1u << e;
+      const uint32_t i = tid + kFiltBS * e;
+      uk[e] = a.union_keys[min(i, a.union_n - 1)];
+      if (i < a.union_n) valid |= 1u << e;
     }
+    cutv = a.cut[min(tid, a.n_cut - 1)];
   }
   u32x4 v[U];
   auto load_step = [&](uint32_t vb, uint32_t fill) {
@@ -87,46 +93,33 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
       else v[u] = u32x4{fill, fill, fill, fill};
     }
   };
-  // 0xFFFFFFFF is the lowest key: it fails the fast test unless every key
-  // passes, and the exact test skips slots past the end anyway.
-  load_step(vbeg, 0xFFFFFFFFu);
+  // The first step: past the end the last vector is read again, and the
+  // exact test skips it (an input of no whole vector reads the call state).
+  // Without a branch the compiler can count the loads in flight, and waits
+  // for the union only and not for the step.
+  {
+    const u32x4* const first = vend ? vec : reinterpret_cast<const u32x4*>(a.st);
+    const uint32_t last = vend ? vend - 1 : 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(first + min(vbeg + u * kFiltBS + tid, last));
+  }
 
-  // ---- threshold (stage 2) when the sample union is small (t <= 32)
+  // ---- threshold (stage 2) when the sample union is small
   uint32_t tau;
   if (a.union_n) {
-    uint32_t last = 0;
-    if (one_wave) {
-      // one wave holds the whole union in registers
-      if (tid < kWave) {
-        wave_top_t<E>(uk, valid, a.t, nullptr, last);
-        if (lane == 0) s_tau = last;
-      }
-    } else {
-      // every wave keeps the top t of its share, wave 0 merges the lists
-      constexpr int NW = kFiltBS / kWave;
-      const uint32_t w = tid / kWave;
-      const uint32_t got = wave_top_t<E>(uk, valid, a.t, s_lists + w * kWaveTopMax, last);
-      if (lane == 0) s_found[w] = got;
-      __syncthreads();
-      if (w == 0) {
-        constexpr int E2 = NW * kWaveTopMax / kWave;
-        uint32_t v2[E2];
-        uint32_t valid2 = 0;
-#pragma unroll
-        for (int e = 0; e < E2; ++e) {
-          uint32_t c = lane + kWave * e, li = 0;
-          v2[e] = 0;
-#pragma unroll
-          for (int i = 0; i < NW; ++i)
-            if (li == static_cast<uint32_t>(i) && c >= s_found[i]) { c -= s_found[i]; li = i + 1; }
-          if (li < NW) { v2[e] = s_lists[li * kWaveTopMax + c]; valid2 |= 1u << e; }
-        }
-        wave_top_t<E2>(v2, valid2, a.t, nullptr, last);
-        if (lane == 0) s_tau = last;
-      }
+    tau = block_kth_regs<kFiltBS, E, kTauDigit>(uk, valid, a.t, s_pool, s_pool + (1u << kTauDigit), s_red, s_sc).x;
+    if (a.all_keys)
+      for (uint32_t i = tid + kFiltBS; i < a.n_cut; i += kFiltBS) cutv = max(cutv, a.cut[i]);
+    if (a.all_keys && tau <= block_max<kFiltBS>(cutv, s_sc.wsum)) {
+      // some block may have dropped a key above tau: all sample keys
+      static_assert(kSelBins <= kLogBins, "histogram of the select");
+      tau = block_select_kth<kFiltBS, kSelDigit>(
+                [&](auto f) {
+                  for_items<kFiltBS, 8>(a.n_all, [&](uint32_t i) { return a.all_keys[i]; }, [&](uint32_t, uint32_t x) { f(x); });
+                },
+                a.t, Elem<DT>::KEYBITS, 0u, s_pool, s_sc)
+                .kth;
     }
-    __syncthreads();
-    tau = s_tau;
     if (b == 0 && tid == 0) a.st->tau_key = tau;
   } else {
     tau = a.st->tau_key;
@@ -271,6 +264,9 @@ static hipError_t launch_filter_t(const FlatCall& c, CallState* st, const uint32
   const uint32_t nvec = (c.n - head) / EPV;
   FilterArgs fa{c.values, c.n, head, nvec, L.seg_cap, st,
                 union_keys, union_keys ? L.union_n : 0u, static_cast<uint32_t>(c.plan->t),
+                L.cap_list ? at<uint32_t>(c.ws, L.off_cut) : union_keys, L.cap_list ? L.G_s : 1u,
+                union_keys && L.cap_list ? at<uint32_t>(c.ws, L.off_all_keys) : nullptr,
+                static_cast<uint32_t>(c.plan->S),
                 at<uint32_t>(c.ws, L.off_segcnt), at<uint32_t>(c.ws, L.off_seg_key),
                 at<uint32_t>(c.ws, L.off_seg_idx), at<uint32_t>(c.ws, L.off_blk_max),
                 at<uint32_t>(c.ws, L.off_fhist)};

@@ -76,8 +76,8 @@ __global__ __launch_bounds__(BS) void k_sample(SampleArgs a) {
         if ((valid >> q) & 1u) a.all_keys[j0 + 4 * tid + q] = kv[q];
     }
   }
-  sample_block_top<BS, Elem<DT>::KEYBITS>(kv, valid, nb, a.t, a.union_keys + static_cast<size_t>(b) * a.tcap, sh,
-                                           a.cut ? a.cut + b : nullptr);
+  sample_block_top<BS>(kv, valid, nb, a.t, a.union_keys + static_cast<size_t>(b) * a.tcap, sh,
+                       a.cut ? a.cut + b : nullptr);
 }
 
 // Per-block top-t of keys already in memory (the SAE path's sampled
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(BS) void k_key_union(const uint32_t* keys, uint32_t
     kv[q] = j < nb ? keys[j0 + j] : 0u;
     if (j < nb) valid |= 1u << q;
   }
-  sample_block_top<BS, 32>(kv, valid, nb, t, union_keys + static_cast<size_t>(b) * tcap, sh);
+  sample_block_top<BS>(kv, valid, nb, t, union_keys + static_cast<size_t>(b) * tcap, sh);
 }
 
 // ------------------------------------------------------------ stage 2 -----
@@ -122,69 +122,46 @@ struct TauArgs {
 };
 
 __global__ __launch_bounds__(kTauBS) void k_select_tau(TauArgs a) {
-  constexpr int NW = kTauBS / kWave;
-  constexpr int E = 8;  // union keys per lane on the wave path
+  constexpr int E = 8;  // keys per thread when the union is held in registers
   __shared__ uint32_t cache[kTauCache];
   __shared__ SelectShared sel;
-  __shared__ uint32_t lists[NW][kWaveTopMax];
-  __shared__ uint32_t list_n[NW];
+  __shared__ uint32_t list_n[2];
   __shared__ uint32_t tlist[kTauList];
-  const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  if (a.t <= kWaveTopMax && a.n <= static_cast<uint32_t>(kTauBS * E)) {
-    // every wave keeps the top t of its share, wave 0 merges the lists
-    uint32_t v[E];
-    uint32_t valid = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const uint32_t i = w * (kWave * E) + e * kWave + lane;
-      v[e] = i < a.n ? a.keys[i] : 0u;
-      if (i < a.n) valid |= 1u << e;
-    }
-    uint32_t last = 0;
-    const uint32_t got = wave_top_t<E>(v, valid, a.t, lists[w], last);
-    if (lane == 0) list_n[w] = got;
-    __syncthreads();
-    if (w == 0) {
-      constexpr int E2 = NW * kWaveTopMax / kWave;
-      uint32_t v2[E2];
-      uint32_t valid2 = 0;
-#pragma unroll
-      for (int e = 0; e < E2; ++e) {
-        uint32_t c = lane + kWave * e, li = 0;
-        v2[e] = 0;
-#pragma unroll
-        for (int i = 0; i < NW; ++i)
-          if (li == static_cast<uint32_t>(i) && c >= list_n[i]) { c -= list_n[i]; li = i + 1; }
-        if (li < NW) { v2[e] = lists[li][c]; valid2 |= 1u << e; }
-      }
-      wave_top_t<E2>(v2, valid2, a.t, nullptr, last);
-      if (lane == 0) a.st->tau_key = last;
-    }
-    return;
-  }
+  __shared__ uint32_t red[2 * (kTauBS / kWave) + 2];
+  const uint32_t tid = threadIdx.x;
+  // A union of at most 8*kTauBS keys is selected from registers; larger ones
+  // by digit passes over LDS or memory.
   // Capped sample lists: the t-th largest of the union is the sample's
   // unless a block that dropped keys has its cut key at or above it (every
-  // dropped key is at most its block's cut key).  With C the largest cut
-  // key, that is the case exactly when fewer than t union keys exceed C; the
-  // select then takes all sample keys instead.
+  // dropped key is at most its block's cut key), i.e. unless fewer than t
+  // union keys exceed the largest cut key; the select then takes all sample
+  // keys instead.
   const uint32_t* keys = a.keys;
   uint32_t n = a.n;
-  if (a.cut) {
-    // the first 4*kTauBS union keys are loaded with the cut keys
-    constexpr int U = 4;
-    uint32_t u[U];
+  if (n <= static_cast<uint32_t>(kTauBS * E)) {
+    uint32_t v[E];
+    uint32_t valid = 0, c = 0;
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const uint32_t i = j * kTauBS + tid;
-      u[j] = i < a.n ? a.keys[i] : 0u;
+    for (int e = 0; e < E; ++e) {
+      const uint32_t i = e * kTauBS + tid;
+      v[e] = i < n ? keys[i] : 0u;
+      if (i < n) valid |= 1u << e;
     }
+    if (a.cut)
+      for (uint32_t i = tid; i < a.n_cut; i += kTauBS) c = max(c, a.cut[i]);
+    const uint32_t kth = block_kth_regs<kTauBS, E, kSelDigit>(v, valid, a.t, sel.hist, tlist, red, sel.scratch()).x;
+    if (!a.cut || kth > block_max<kTauBS>(c, sel.wsum)) {
+      if (tid == 0) a.st->tau_key = kth;
+      return;
+    }
+    keys = a.all_keys;
+    n = a.n_all;
+  } else if (a.cut) {
     uint32_t c = 0;
     for (uint32_t i = tid; i < a.n_cut; i += kTauBS) c = max(c, a.cut[i]);
     c = block_max<kTauBS>(c, sel.wsum);
     uint32_t above = 0;
-#pragma unroll
-    for (int j = 0; j < U; ++j) above += (j * kTauBS + tid < a.n && u[j] > c) ? 1u : 0u;
-    for (uint32_t i = U * kTauBS + tid; i < a.n; i += kTauBS) above += a.keys[i] > c ? 1u : 0u;
+    for_items<kTauBS, 8>(n, [&](uint32_t i) { return keys[i]; }, [&](uint32_t, uint32_t v) { above += v > c ? 1u : 0u; });
     // (the same in every thread: readfirstlane keeps the source uniform for
     // the compiler)
     if (__builtin_amdgcn_readfirstlane(block_sum<kTauBS>(above, sel.wsum)) < a.t) {
@@ -1002,13 +979,13 @@ static inline uint32_t cdiv(uint64_t a, uint64_t b) { return static_cast<uint32_
 static inline size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 // Length of the capped sample lists for a key-rule plan with t >
-// kWaveTopMax, or 0 when the draws of a block in the top t are too many for
-// kWaveTopMax to hold them with a margin of eight standard deviations.
+// kCapListMax, or 0 when the draws of a block in the top t are too many for
+// kCapListMax to hold them with a margin of eight standard deviations.
 static uint32_t capped_list_len(uint32_t S, uint32_t t, bool lex) {
-  if (lex || t <= kWaveTopMax || S < 2u * kSampPerBlock) return 0;
+  if (lex || t <= kCapListMax || S < 2u * kSampPerBlock) return 0;
   const double mu = static_cast<double>(kSampPerBlock) * t / S;
   const double need = mu + 8.0 * std::sqrt(mu) + 2.0;
-  return need <= kCapListSmall ? kCapListSmall : (need <= kWaveTopMax ? kWaveTopMax : 0u);
+  return need <= kCapListSmall ? kCapListSmall : (need <= kCapListMax ? kCapListMax : 0u);
 }
 
 FlatLayout flat_layout(const profk_plan_t& p, int dtype, int num_cus) {
@@ -1018,7 +995,7 @@ FlatLayout flat_layout(const profk_plan_t& p, int dtype, int num_cus) {
   const uint32_t S = static_cast<uint32_t>(p.S), t = static_cast<uint32_t>(p.t);
   const uint32_t M = static_cast<uint32_t>(p.M), k = static_cast<uint32_t>(p.k);
   L.cap_list = capped_list_len(S, t, p.lexicographic != 0);
-  L.samp_bs = (!p.lexicographic && t > kWaveTopMax && !L.cap_list) ? kSampWideBS : kSampBS;
+  L.samp_bs = (!p.lexicographic && t > kCapListMax && !L.cap_list) ? kSampWideBS : kSampBS;
   const uint32_t spb = 4u * L.samp_bs;
   const uint32_t tl = L.cap_list ? L.cap_list : t;  // length of a block's list
   L.G_s = cdiv(S, spb);
@@ -1141,7 +1118,7 @@ static hipError_t launch_flat_t(const FlatCall& c) {
                   L.cap_list ? at<uint32_t>(c.ws, L.off_all_keys) : nullptr};
     if (L.samp_bs == kSampWideBS) hipLaunchKernelGGL((k_sample<DT, kSampWideBS>), dim3(L.G_s), dim3(kSampWideBS), 0, c.stream, sa);
     else hipLaunchKernelGGL((k_sample<DT, kSampBS>), dim3(L.G_s), dim3(kSampBS), 0, c.stream, sa);
-    if (!lex && L.union_n <= kFiltTauMax && static_cast<uint32_t>(p.t) <= kFiltTauInMaxT) {
+    if (!lex && L.union_n <= kFiltTauMax) {
       union_for_filter = uk;
     } else {
       TauArgs ta{uk, L.union_n, static_cast<uint32_t>(p.t), Elem<DT>::KEYBITS, st,

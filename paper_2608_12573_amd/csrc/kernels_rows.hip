@@ -22,11 +22,8 @@
 
 namespace profk {
 
-// tau from the sample held in registers (at most 8 keys per thread): each
-// wave's top-t, then the top-t of their union.
-__host__ __device__ constexpr bool row_fast_tau(uint32_t S, uint32_t t) {
-  return S <= 8u * kRowBS && t >= 1 && t <= kWaveTopMax;
-}
+// The sample is held in registers (at most 8 keys per thread).
+__host__ __device__ constexpr bool row_fast_tau(uint32_t S) { return S <= 8u * kRowBS; }
 
 struct RowArgs {
   const void* values;
@@ -45,6 +42,7 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
   constexpr int ES = Elem<DT>::ES, EPV = Elem<DT>::EPV, KB = Elem<DT>::KEYBITS;
   constexpr int kSelDigitRow = KB == 16 ? 8 : 11;  // sample select: 2 or 3 passes
   constexpr int kDigit = row_digit<DT>();
+  constexpr int kTauDigit = KB == 16 ? 8 : 10;         // the sample's histogram, within `hist`
   using K = RowKey<DT>;
   constexpr int NW = kRowBS / kWave;
   constexpr uint32_t NB = row_log_bins<DT>();
@@ -59,7 +57,7 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
   uint64_t* const comp = reinterpret_cast<uint64_t*>(smem + a.L.off_comp);
   uint64_t* const exch = reinterpret_cast<uint64_t*>(smem + a.L.off_a);      // after the buffer is done
   __shared__ SelectScratch scr;
-  __shared__ uint32_t s_cnt, s_counter, s_tau, s_tie_n, s_wmax[NW];
+  __shared__ uint32_t s_cnt, s_counter, s_tie_n, s_wmax[NW], s_red[2 * NW + 2];
 
   const uint32_t r = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   const char* row = static_cast<const char*>(a.values) + static_cast<size_t>(r) * a.row_stride * ES;
@@ -71,7 +69,7 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
   uint32_t status = PROFK_STATUS_DIRECT, count = 0, tau = 0, gmax = 0;
   if (!a.direct) {
     // 1. sample: the Philox words first, then all gathers in flight at once
-    const bool fast = row_fast_tau(a.S, a.t);
+    const bool fast = row_fast_tau(a.S);
     uint32_t keys[8], ids[8];
     uint32_t valid = 0;
     for (uint32_t blk0 = 0; 4 * blk0 < a.S; blk0 += 2 * kRowBS) {
@@ -105,27 +103,7 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
     if (tid == 0) s_cnt = 0;
     // 2. threshold
     if (fast) {
-      // every wave's top-t (hist serves as scratch: NW lists of up to
-      // kWaveTopMax keys, then their lengths), then the top-t of the union
-      uint32_t last = 0;
-      const uint32_t got = wave_top_t<8>(keys, valid, a.t, hist + w * kWaveTopMax, last);
-      if (lane == 0) hist[NW * kWaveTopMax + w] = got;
-      __syncthreads();
-      if (w == 0) {
-        static_assert(NW * kWaveTopMax == 2 * kWave, "union of the wave lists: two keys per lane");
-        uint32_t u[2];
-        uint32_t uv = 0;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const uint32_t s = lane + q * kWave, ww = s / kWaveTopMax;
-          u[q] = hist[s];
-          if (s % kWaveTopMax < hist[NW * kWaveTopMax + ww]) uv |= 1u << q;
-        }
-        wave_top_t<2>(u, uv, a.t, nullptr, last);
-        if (lane == 0) s_tau = last;
-      }
-      __syncthreads();
-      tau = s_tau;
+      tau = block_kth_regs<kRowBS, 8, kTauDigit>(keys, valid, a.t, hist, reinterpret_cast<uint32_t*>(comp), s_red, scr).x;
     } else {
       __syncthreads();
       tau = block_select_kth<kRowBS, kSelDigitRow>(
@@ -325,15 +303,13 @@ RowLayout row_layout(const profk_plan_t& p, int dtype) {
   while (P < (k > static_cast<uint32_t>(kRowBS) ? k : static_cast<uint32_t>(kRowBS))) P <<= 1;
   const uint32_t exch = 2u * P * 8u;
   const uint32_t b_bytes = align16(M * 4u);
-  const uint32_t samp_bytes = row_fast_tau(S, t) ? 0u : S * 4u;   // samples kept in LDS
+  const uint32_t samp_bytes = (row_fast_tau(S) && t <= kCapListMax) ? 0u : S * 4u;   // samples kept in LDS
   const uint32_t key_bytes = M * (f32 ? 4u : 2u);
   uint32_t a_bytes = align16(samp_bytes > key_bytes ? samp_bytes : key_bytes);
   if (a_bytes + b_bytes < exch) a_bytes = exch - b_bytes;
   const uint32_t nb = f32 ? row_log_bins<0>() : row_log_bins<1>();
   const uint32_t radix = 1u << (f32 ? row_digit<0>() : row_digit<1>());
   uint32_t hist_words = radix > nb ? radix : nb;
-  if (hist_words < static_cast<uint32_t>(kRowBS / kWave) * (kWaveTopMax + 1))
-    hist_words = static_cast<uint32_t>(kRowBS / kWave) * (kWaveTopMax + 1);
   L.off_a = 0;
   L.off_b = a_bytes;
   L.off_hist = L.off_b + b_bytes;

@@ -29,12 +29,12 @@ static_assert(sizeof(CallState) == 256, "call state size");
 constexpr uint32_t kXcds = 8;                 // MI355X: 8 XCDs of 32 CUs, each with its own L2
 constexpr int kSampBS = 256;                  // threads of a sample block
 constexpr int kSampPerBlock = 4 * kSampBS;    // draws per sample block
-// Sample blocks of plans with t > kWaveTopMax (key rule): 1024 threads and
+// Sample blocks of plans with t > kCapListMax (key rule): 1024 threads and
 // 4096 draws, so that the union of the blocks' top-t lists, which one
 // workgroup selects tau from, is four times smaller.
 constexpr int kSampWideBS = 1024;
-constexpr uint32_t kWaveTopMax = 32;          // largest t of the wave-level top-t
-// Capped sample lists (key rule, t > kWaveTopMax): when the draws of one
+constexpr uint32_t kCapListMax = 32;          // longest capped list; smaller t need none
+// Capped sample lists (key rule, t > kCapListMax): when the draws of one
 // 1024-draw block that lie in the sample's top t are few (mean mu = 1024 t /
 // S), each block keeps only its top c (c = 16 or 32, at least mu + 8
 // sqrt(mu) + 2) and its c-th largest key, and the blocks store every key.
@@ -60,10 +60,11 @@ constexpr int kFiltPerCuSparse = 2;
 constexpr int kFiltPerCuDense = 4;
 constexpr uint64_t kFiltSparseMinBytes = 512ull << 20;  // "large"
 constexpr uint64_t kFiltSparseInvDensity = 4096;        // "rare": t/(S+1) below 1/4096
-constexpr uint32_t kFiltTauMax = 2048;        // largest sample union a filter block selects from
-constexpr uint32_t kFiltTauWave = 4;          // union keys per lane when one wave selects tau
-constexpr uint32_t kFiltTauInMaxT = 32;       // largest t the filter blocks select tau for themselves
-static_assert(kFiltTauInMaxT <= kWaveTopMax, "the filter selects tau with the wave-level top-t");
+// Largest sample union a filter block selects tau from: eight keys per
+// thread in registers, whatever t.  The select is about 2.5 us at the start
+// of every block and overlaps its first loads, where k_select_tau is a
+// launch of 9 us (BatchTopK, 2^28 values, t = 188: 223 -> 214 us).
+constexpr uint32_t kFiltTauMax = 2048;
 constexpr uint32_t kStage = 1024;             // survivors a filter block stages in LDS
 constexpr int kSegs = 8;                      // candidate segments (one counter each)
 constexpr int kSegStride = 64;                // words between segment counters

@@ -35,107 +35,51 @@ __device__ __forceinline__ void reset_state(CallState* st, uint32_t* seg_cnt, ui
   if (threadIdx.x < 16) st->grp_ticket[threadIdx.x] = 0;
 }
 
+// LDS of sample_block_top.
 template <int BS>
 struct SampleUnionShared {
-  uint32_t keys[4 * BS];
-  uint32_t lists[BS / kWave][kWaveTopMax];
-  uint32_t list_n[BS / kWave];
-  uint32_t bin_list[kListRankMax];  // t > kWaveTopMax: the keys of the bin holding rank t
-  uint32_t kth[2];
-  SelectShared sel;
+  static constexpr int kDigit = BS <= kSampBS ? 10 : 11;  // about a bin per draw, half a bin on wide blocks
+  alignas(16) uint32_t hist[1 << kDigit];
+  uint32_t bin_list[kListRankMax];  // the keys of the bin holding rank t
+  uint32_t red[2 * (BS / kWave) + 2];
+  SelectScratch sc;
   uint32_t emitted;
 };
 
-// Writes the workgroup's top-min(t, nb) draws to dst (nb: draws it holds,
-// valid bit q of `valid` for kv[q]).  Every thread of the workgroup calls it.
-// With t <= kWaveTopMax, *cut (when not null) receives the t-th largest
+// Writes the workgroup's top-min(t, nb) draws to dst, in no particular order
+// (nb: draws it holds, valid bit q of `valid` for kv[q]).  Every thread of
+// the workgroup calls it.  *cut (when not null) receives the t-th largest
 // draw if the workgroup dropped any (nb > t), else 0.
-template <int BS, int KEYBITS>
+template <int BS>
 __device__ __forceinline__ void sample_block_top(uint32_t (&kv)[4], uint32_t valid, uint32_t nb, uint32_t t,
                                                  uint32_t* dst, SampleUnionShared<BS>& sh,
                                                  uint32_t* cut = nullptr) {
-  constexpr int NW = BS / kWave;
-  static_assert(NW * kWaveTopMax % kWave == 0, "union of the wave lists");
-  const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const uint32_t tl = min(t, nb);
-  if (t <= kWaveTopMax) {
-    // each wave keeps its top-tl draws, then wave 0 merges the NW lists
-    uint32_t last;
-    const uint32_t got = wave_top_t<4>(kv, valid, tl, sh.lists[w], last);
-    if (lane == 0) sh.list_n[w] = got;
-    __syncthreads();
-    if (w == 0) {
-      constexpr int E2 = NW * kWaveTopMax / kWave;
-      uint32_t v2[E2];
-      uint32_t valid2 = 0;
+  const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
+  if (t >= nb) {
 #pragma unroll
-      for (int e = 0; e < E2; ++e) {
-        // concatenated list position c = lane + 64*e
-        uint32_t c = lane + kWave * e, li = 0;
-        v2[e] = 0;
-#pragma unroll
-        for (int i = 0; i < NW; ++i)
-          if (li == static_cast<uint32_t>(i) && c >= sh.list_n[i]) { c -= sh.list_n[i]; li = i + 1; }
-        if (li < NW) { v2[e] = sh.lists[li][c]; valid2 |= 1u << e; }
-      }
-      wave_top_t<E2>(v2, valid2, tl, dst, last);
-      if (cut && lane == 0) *cut = nb > tl ? last : 0u;
-    }
+    for (int q = 0; q < 4; ++q)
+      if ((valid >> q) & 1u) dst[4 * tid + q] = kv[q];
+    if (cut && tid == 0) *cut = 0u;
     return;
   }
+  if (tid == 0) sh.emitted = 0;  // (the select's barriers order it)
+  const uint2 r = block_kth_regs<BS, 4, SampleUnionShared<BS>::kDigit>(kv, valid, t, sh.hist, sh.bin_list, sh.red, sh.sc);
+  // the keys above the t-th, then copies of it up to t
+  uint32_t m = 0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if ((valid >> q) & 1u) sh.keys[4 * tid + q] = kv[q];
-  __syncthreads();
-  if (tl == nb) {
-    for (uint32_t j = tid; j < nb; j += BS) dst[j] = sh.keys[j];
-    return;
-  }
-  // One digit pass over the top key bits finds the bin holding rank tl;
-  // when it holds few keys they are ranked by counting, otherwise the
-  // remaining digits are taken over all keys.
-  constexpr int SHIFT = KEYBITS - kSelDigit;
-  for (uint32_t i = tid; i < static_cast<uint32_t>(kSelBins); i += BS) sh.sel.hist[i] = 0;
-  if (tid == 0) {
-    sh.emitted = 0;
-    sh.list_n[0] = 0;
-  }
-  __syncthreads();
+  for (int q = 0; q < 4; ++q) m |= (((valid >> q) & 1u) && kv[q] > r.x ? 1u : 0u) << q;
+  const uint32_t c = static_cast<uint32_t>(__popc(m)), incl = wave_incl_sum(c);
+  const uint32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
+  if (tot) {
+    uint32_t slot = 0;
+    if (lane == 0) slot = atomicAdd(&sh.emitted, tot);
+    slot = __builtin_amdgcn_readlane(slot, 0) + incl - c;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) hist_add(sh.sel.hist, kv[q] >> SHIFT, (valid >> q) & 1u);
-  __syncthreads();
-  if (tid < kWave) rank_bin_search(sh.sel.hist, kSelBins, tl, sh.sel.scratch());
-  __syncthreads();
-  const uint32_t d = sh.sel.found[0], above = sh.sel.found[1], eq = sh.sel.found[2];
-  uint32_t kth, above_kth;
-  if (eq <= kListRankMax) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const bool take = ((valid >> q) & 1u) && (kv[q] >> SHIFT) == d;
-      const uint32_t slot = lds_append(&sh.list_n[0], take);
-      if (take) sh.bin_list[slot] = kv[q];
-    }
-    __syncthreads();
-    list_kth<BS>(sh.bin_list, eq, tl - above, sh.kth);
-    __syncthreads();
-    kth = sh.kth[0];
-    above_kth = above + sh.kth[1];
-  } else {
-    auto visit = [&](auto f) {
-      for (uint32_t j = tid; j < nb; j += BS) f(sh.keys[j]);
-    };
-    const SelectResult r = block_select_kth<BS>(visit, tl - above, SHIFT, d << SHIFT, sh.sel);
-    kth = r.kth;
-    above_kth = above + r.above;
+    for (int q = 0; q < 4; ++q)
+      if ((m >> q) & 1u) dst[slot++] = kv[q];
   }
-  // the keys above the tl-th, then copies of it up to tl
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const bool take = ((valid >> q) & 1u) && kv[q] > kth;
-    const uint32_t slot = lds_append(&sh.emitted, take);
-    if (take) dst[slot] = kv[q];
-  }
-  for (uint32_t j = above_kth + tid; j < tl; j += BS) dst[j] = kth;
+  for (uint32_t j = r.y + tid; j < t; j += BS) dst[j] = r.x;
+  if (cut && tid == 0) *cut = r.x;
 }
 
 }  // namespace profk

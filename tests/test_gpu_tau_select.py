@@ -1,0 +1,73 @@
+"""GPU parity of the threshold select: tau, count and status of whole calls
+against the oracle, bit-exact, on inputs that drive the select's cases: a
+bin of rank t that is one key wide (ties), one that holds few keys, one that
+holds more than a counted list and is split again (values packed in a few
+adjacent bit patterns beside an outlier), keys over the whole range, t = 1
+and t at the union's end; in the filter (small unions, and capped lists with
+and without the cut check failing), in the select launch (large unions) and
+in the row kernel."""
+
+import dataclasses
+
+import numpy as np
+import pytest
+
+import paper_2608_12573_amd as pk
+import workloads
+from oracle import keys as okeys, plan as oplan, profk as oprofk
+from gpu_util import check_rows, compare, gpu_f32, note, oracle_plan_of
+
+pytestmark = pytest.mark.gpu
+
+
+def _values(kind, n, seed):
+    g = np.random.default_rng(seed)
+    if kind == "normal":
+        return g.standard_normal(n, dtype=np.float32)
+    if kind == "zeros":        # nearly every sampled key is the same
+        x = np.zeros(n, dtype=np.float32)
+        x[g.choice(n, n // 50, replace=False)] = g.random(n // 50, dtype=np.float32)
+        return x
+    if kind == "packed":       # 4096 adjacent patterns, one huge value and one of each infinity
+        u = (np.uint32(0x3F800000) + g.integers(0, 4096, n).astype(np.uint32)).view(np.float32).copy()
+        u[g.integers(0, n, 3)] = [1e38, np.inf, -np.inf]
+        return u
+    if kind == "wide":         # every exponent and sign
+        u = g.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+        return u.view(np.float32).copy()
+    raise ValueError(kind)
+
+
+def _check(x, k, seed, **kw):
+    p = pk.plan(x.size, k, **kw)
+    q = oracle_plan_of(p, **kw)
+    note(f"vec N={x.size} k={k} S={p.S} t={p.t} M={p.M}")
+    vals, idx, info = pk.topk(gpu_f32(x), k, seed=seed, p=p)
+    compare(vals, idx, info, oprofk.run(okeys.f32_bits(x), "f32", k, q, seed), "f32")
+
+
+@pytest.mark.parametrize("kind", ["normal", "zeros", "packed", "wide"])
+@pytest.mark.parametrize("N,k", [(70001, 1), (2**18 + 3, 40), (2**20, 2000), (2**20, 9000), (2**18, 16384)])
+def test_vector_tau(kind, N, k):
+    """t from 3 to about 2000: unions in the filter's registers, capped lists,
+    and unions that take the select launch."""
+    _check(_values(kind, N, N % 1009 + k), k, 3)
+
+
+@pytest.mark.parametrize("S,k", [(33, 1), (256, 3), (257, 8), (1025, 60), (2049, 200)])
+def test_vector_tau_small_samples(S, k):
+    """Partial sample blocks down to one key above a block's size."""
+    _check(_values("normal", 50001, S), k, 1, S_min=S, S_max=S, force_mode=pk.FORCE_FILTER)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,k,S", [(3001, 1, 64), (3001, 64, 300), (9001, 200, 2048), (9001, 200, 2049), (20001, 900, 4000)])
+def test_row_tau(dtype, D, k, S):
+    """Samples in registers (up to 2048 draws on 256 threads) and in LDS."""
+    x = np.concatenate([_values(kind, D, D + k) for kind in ("normal", "zeros", "packed")]).reshape(3, D)
+    bits = okeys.f32_bits(x) if dtype == "f32" else workloads.f32_to_bf16_bits(
+        np.where(np.isfinite(x), x, np.float32(0)))
+    kw = dict(S_min=S, S_max=S, force_mode=pk.FORCE_FILTER)
+    p = pk.plan_rows(D, k, **kw)
+    q = oracle_plan_of(p, opts=dataclasses.replace(oplan.ROW_OPTS, S_min=S, S_max=S, force_mode=pk.FORCE_FILTER))
+    check_rows(bits.reshape(3, D), dtype, k, p, q, 2)
