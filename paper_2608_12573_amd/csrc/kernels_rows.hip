@@ -23,7 +23,11 @@
 namespace profk {
 
 // The sample is held in registers (at most 8 keys per thread).
-__host__ __device__ constexpr bool row_fast_tau(uint32_t S) { return S <= 8u * kRowBS; }
+__host__ __device__ constexpr bool row_fast_tau(uint32_t S, int bs) { return S <= 8u * static_cast<uint32_t>(bs); }
+
+// Log-scale buckets of a row workgroup: the buckets of a row key's distance,
+// padded so that every thread owns the same number.
+template <int DT, int BS> constexpr uint32_t row_bins_per_thread() { return (row_log_bins<DT>() + BS - 1) / BS; }
 
 struct RowArgs {
   const void* values;
@@ -37,17 +41,19 @@ struct RowArgs {
   RowLayout L;
 };
 
-template <int DT, bool LEX>
-__global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
+// PRE: the first step of the row's stream is loaded before the sample is
+// drawn, so that the sample's latency and the stream's overlap; it takes
+// registers that a workgroup among many on its CU has no use for.
+template <int DT, bool LEX, int BS, bool PRE>
+__global__ __launch_bounds__(BS) void k_rows(RowArgs a) {
   constexpr int ES = Elem<DT>::ES, EPV = Elem<DT>::EPV, KB = Elem<DT>::KEYBITS;
   constexpr int kSelDigitRow = KB == 16 ? 8 : 11;  // sample select: 2 or 3 passes
   constexpr int kDigit = row_digit<DT>();
   constexpr int kTauDigit = KB == 16 ? 8 : 10;         // the sample's histogram, within `hist`
   using K = RowKey<DT>;
-  constexpr int NW = kRowBS / kWave;
-  constexpr uint32_t NB = row_log_bins<DT>();
-  constexpr uint32_t RB = NB / kRowBS;              // log bins owned per thread
-  static_assert(NB % kRowBS == 0, "log-bin ownership");
+  constexpr int NW = BS / kWave;
+  constexpr uint32_t RB = row_bins_per_thread<DT, BS>();  // log bins owned per thread
+  constexpr uint32_t NB = RB * BS;                        // (the bins past the last log bin stay empty)
   extern __shared__ __align__(16) uint8_t smem[];
   uint32_t* const samp = reinterpret_cast<uint32_t*>(smem + a.L.off_a);  // samples, then buffer keys
   K* const bkey = reinterpret_cast<K*>(smem + a.L.off_a);
@@ -66,17 +72,33 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
   const uint32_t key_max = KB == 32 ? 0xFFFFFFFFu : 0xFFFFu;
   const TopkSmem sm{nullptr, 0, hist, collect, &scr, &s_counter};
 
+  const uintptr_t addr = reinterpret_cast<uintptr_t>(row);
+  uint32_t head = static_cast<uint32_t>(((16 - (addr & 15)) & 15) / ES);
+  if (head > a.D) head = a.D;
+  const uint32_t nvec = (a.D - head) / EPV;
+  const u32x4* vec = reinterpret_cast<const u32x4*>(row + static_cast<size_t>(head) * ES);
+
   uint32_t status = PROFK_STATUS_DIRECT, count = 0, tau = 0, gmax = 0;
   if (!a.direct) {
+    u32x4 v[kRowU];
+    // one step of the stream, kRowU vectors per thread (nvec > 0): past the
+    // end the last vector is read again, and the exact test skips it.
+    // (branch-free: with a branch per vector and v outside the loop the
+    // compiler waits for each load before it issues the next)
+    auto load_step = [&](uint32_t vb) {
+#pragma unroll
+      for (int u = 0; u < kRowU; ++u) v[u] = __builtin_nontemporal_load(vec + min(vb + u * BS + tid, nvec - 1));
+    };
+    if (PRE && nvec) load_step(0);
     // 1. sample: the Philox words first, then all gathers in flight at once
-    const bool fast = row_fast_tau(a.S);
+    const bool fast = row_fast_tau(a.S, BS);
     uint32_t keys[8], ids[8];
     uint32_t valid = 0;
-    for (uint32_t blk0 = 0; 4 * blk0 < a.S; blk0 += 2 * kRowBS) {
+    for (uint32_t blk0 = 0; 4 * blk0 < a.S; blk0 += 2 * BS) {
       U64x4 rnd[2];
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        const uint32_t blk = blk0 + q * kRowBS + tid;
+        const uint32_t blk = blk0 + q * BS + tid;
         if (4 * blk < a.S) rnd[q] = philox4x64_10(blk, r, 0, 0, a.seed, 0);
       }
       uint32_t raw[8];
@@ -84,7 +106,7 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
       for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-          const uint32_t j = 4 * (blk0 + q * kRowBS + tid) + x;
+          const uint32_t j = 4 * (blk0 + q * BS + tid) + x;
           ids[4 * q + x] = j < a.S ? index_of_word(rnd[q].w[x], a.D) : 0u;
           raw[4 * q + x] = j < a.S ? load_raw<DT>(row, ids[4 * q + x]) : 0u;
         }
@@ -92,7 +114,7 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
       for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-          const uint32_t j = 4 * (blk0 + q * kRowBS + tid) + x;
+          const uint32_t j = 4 * (blk0 + q * BS + tid) + x;
           keys[4 * q + x] = key_of<DT>(raw[4 * q + x]);
           if (j < a.S) {
             valid |= 1u << (4 * q + x);
@@ -103,12 +125,12 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
     if (tid == 0) s_cnt = 0;
     // 2. threshold
     if (fast) {
-      tau = block_kth_regs<kRowBS, 8, kTauDigit>(keys, valid, a.t, hist, reinterpret_cast<uint32_t*>(comp), s_red, scr).x;
+      tau = block_kth_regs<BS, 8, kTauDigit>(keys, valid, a.t, hist, reinterpret_cast<uint32_t*>(comp), s_red, scr).x;
     } else {
       __syncthreads();
-      tau = block_select_kth<kRowBS, kSelDigitRow>(
+      tau = block_select_kth<BS, kSelDigitRow>(
                 [&](auto f) {
-                  for (uint32_t i = tid; i < a.S; i += kRowBS) f(samp[i]);
+                  for (uint32_t i = tid; i < a.S; i += BS) f(samp[i]);
                 },
                 a.t, KB, 0u, hist, scr)
                 .kth;
@@ -121,12 +143,12 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
         for (int e = 0; e < 8; ++e)
           if ((valid >> e) & 1u) f(keys[e], ids[e]);
       };
-      tie = tau_pair_index<kRowBS, kDigit>(draws, tau, a.t, reinterpret_cast<uint32_t*>(smem + a.L.off_a),
+      tie = tau_pair_index<BS, kDigit>(draws, tau, a.t, reinterpret_cast<uint32_t*>(smem + a.L.off_a),
                                            a.L.off_b / 4u, hist, scr, &s_tie_n);
     } else if (LEX) {
       // the draws again (Philox words and gathers), for the tied draws' indices
       auto draws = [&](auto f) {
-        for (uint32_t jb = tid; 4 * jb < a.S; jb += kRowBS) {
+        for (uint32_t jb = tid; 4 * jb < a.S; jb += BS) {
           const U64x4 rr = philox4x64_10(jb, r, 0, 0, a.seed, 0);
           uint32_t raw[4], ix[4];
 #pragma unroll
@@ -140,10 +162,10 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
             if (4 * jb + q < a.S) f(key_of<DT>(raw[q]), ix[q]);
         }
       };
-      tie = tau_pair_index<kRowBS, kDigit>(draws, tau, a.t, reinterpret_cast<uint32_t*>(smem + a.L.off_a),
+      tie = tau_pair_index<BS, kDigit>(draws, tau, a.t, reinterpret_cast<uint32_t*>(smem + a.L.off_a),
                                            a.L.off_b / 4u, hist, scr, &s_tie_n);
     }
-    for (uint32_t i = tid; i < NB; i += kRowBS) hist[i] = 0;
+    for (uint32_t i = tid; i < NB; i += BS) hist[i] = 0;
     __syncthreads();
 
     // 3. filter the row into the LDS buffer (which reuses the sample space)
@@ -163,20 +185,9 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
         bidx[slot] = idx;
       }
     };
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(row);
-    uint32_t head = static_cast<uint32_t>(((16 - (addr & 15)) & 15) / ES);
-    if (head > a.D) head = a.D;
-    const uint32_t nvec = (a.D - head) / EPV;
-    const u32x4* vec = reinterpret_cast<const u32x4*>(row + static_cast<size_t>(head) * ES);
-    for (uint32_t vb = 0; vb < nvec; vb += kRowBS * kRowU) {
-      u32x4 v[kRowU];
-#pragma unroll
-      for (int u = 0; u < kRowU; ++u) {
-        const uint32_t vi = vb + u * kRowBS + tid;
-        if (vi < nvec) v[u] = __builtin_nontemporal_load(vec + vi);
-        else v[u] = u32x4{th.neutral, th.neutral, th.neutral, th.neutral};
-      }
-      const TileSparse<DT, kRowU, kRowBS, LEX> tx(v, th, vb, nvec, tid, head);
+    for (uint32_t vb = 0; vb < nvec; vb += BS * kRowU) {
+      if (!PRE || vb) load_step(vb);
+      const TileSparse<DT, kRowU, BS, LEX> tx(v, th, vb, nvec, tid, head);
       if (__ballot(tx.any()) == 0) continue;
       uint32_t slot = reserve(tx.count());
       tx.emit(v, [&](uint32_t key, uint32_t idx) { store(slot++, key, idx); });
@@ -208,7 +219,7 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
     if (status == PROFK_STATUS_FILTERED) {
       // bucket histogram of the buffer (after the pass, so that the
       // streaming loop does no per-survivor histogram atomics)
-      for (uint32_t i = tid; i < count; i += kRowBS) atomicAdd(&hist[log_bin(bkey[i] - tau)], 1u);
+      for (uint32_t i = tid; i < count; i += BS) atomicAdd(&hist[log_bin(bkey[i] - tau)], 1u);
       __syncthreads();
     }
   }
@@ -228,7 +239,7 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
       h[j] = hist[bb + j];
       s += h[j];
     }
-    uint32_t run = block_excl_sum<kRowBS>(s, scr.wsum, nullptr);
+    uint32_t run = block_excl_sum<BS>(s, scr.wsum, nullptr);
 #pragma unroll
     for (int j = static_cast<int>(RB) - 1; j >= 0; --j) {
       hist[bb + j] = run;
@@ -245,17 +256,17 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
 #pragma unroll
     for (uint32_t j = 0; j < RB; ++j)
       if (bb + j >= bstar) big = max(big, h[j]);
-    big = block_max<kRowBS>(big, scr.wsum);
+    big = block_max<BS>(big, scr.wsum);
     if (n_sel <= a.k + kFastBucket && big <= kFastBucket) {
       // place the buckets >= b*: afterwards hist[b] is the end of bucket b
       // and hist[b + 1] its start
-      for (uint32_t i = tid; i < count; i += kRowBS) {
+      for (uint32_t i = tid; i < count; i += BS) {
         const uint32_t key = bkey[i];
         const uint32_t bin = log_bin(key - tau);
         if (bin >= bstar) comp[atomicAdd(&hist[bin], 1u)] = composite(key, bidx[i]);
       }
       __syncthreads();
-      for (uint32_t p = tid; p < n_sel; p += kRowBS) {
+      for (uint32_t p = tid; p < n_sel; p += BS) {
         const uint64_t c = comp[p];
         const uint32_t bin = log_bin(comp_key(c) - tau);
         const uint32_t s0 = bin + 1 < NB ? hist[bin + 1] : 0u, s1 = hist[bin];
@@ -269,19 +280,19 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
           out_idx[dst] = comp_idx(c);
         }
       }
-      for (uint32_t p = kk + tid; p < a.k; p += kRowBS) {  // relaxed recall: padding
+      for (uint32_t p = kk + tid; p < a.k; p += BS) {  // relaxed recall: padding
         if (DT == 0) static_cast<uint32_t*>(out_vals)[p] = 0xFF800000u;
         else static_cast<uint16_t*>(out_vals)[p] = 0xFF80u;
         out_idx[p] = -1;
       }
       done = true;
     } else {
-      block_topk<kRowBS, kDigit>(LdsSrc<K>{bkey, bidx}, count, kk, tau, max(gmax, tau), KB, sm);
+      block_topk<BS, kDigit>(LdsSrc<K>{bkey, bidx}, count, kk, tau, max(gmax, tau), KB, sm);
     }
   } else {
-    block_topk<kRowBS, kDigit>(InputSrc<DT>{row, 0u}, a.D, a.k, 0u, key_max, KB, sm);
+    block_topk<BS, kDigit>(InputSrc<DT>{row, 0u}, a.D, a.k, 0u, key_max, KB, sm);
   }
-  if (!done) sort_write_any<DT, kRowBS>(collect, kk, a.k, exch, out_vals, out_idx);
+  if (!done) sort_write_any<DT, BS>(collect, kk, a.k, exch, out_vals, out_idx);
   if (a.info && tid == 0) {
     profk_info_t* inf = a.info + r;
     inf->count = count;
@@ -294,22 +305,24 @@ __global__ __launch_bounds__(kRowBS) void k_rows(RowArgs a) {
 // ------------------------------------------------------------- host -------
 static inline uint32_t align16(uint32_t x) { return (x + 15u) & ~15u; }
 
-RowLayout row_layout(const profk_plan_t& p, int dtype) {
+RowLayout row_layout(const profk_plan_t& p, int dtype, int bs) {
   RowLayout L;
   const uint32_t S = static_cast<uint32_t>(p.S), M = static_cast<uint32_t>(p.M);
   const uint32_t k = static_cast<uint32_t>(p.k), t = static_cast<uint32_t>(p.t);
   const bool f32 = dtype == PROFK_F32;
+  const uint32_t ubs = static_cast<uint32_t>(bs);
   uint32_t P = 1;
-  while (P < (k > static_cast<uint32_t>(kRowBS) ? k : static_cast<uint32_t>(kRowBS))) P <<= 1;
+  while (P < (k > ubs ? k : ubs)) P <<= 1;
   const uint32_t exch = 2u * P * 8u;
   const uint32_t b_bytes = align16(M * 4u);
-  const uint32_t samp_bytes = (row_fast_tau(S) && t <= kCapListMax) ? 0u : S * 4u;   // samples kept in LDS
+  const uint32_t samp_bytes = (row_fast_tau(S, bs) && t <= kCapListMax) ? 0u : S * 4u;   // samples kept in LDS
   const uint32_t key_bytes = M * (f32 ? 4u : 2u);
   uint32_t a_bytes = align16(samp_bytes > key_bytes ? samp_bytes : key_bytes);
   if (a_bytes + b_bytes < exch) a_bytes = exch - b_bytes;
-  const uint32_t nb = f32 ? row_log_bins<0>() : row_log_bins<1>();
+  const uint32_t nb = (f32 ? row_log_bins<0>() : row_log_bins<1>()) + ubs - 1;
   const uint32_t radix = 1u << (f32 ? row_digit<0>() : row_digit<1>());
-  uint32_t hist_words = radix > nb ? radix : nb;
+  uint32_t hist_words = radix;
+  if (hist_words < nb / ubs * ubs) hist_words = nb / ubs * ubs;
   L.off_a = 0;
   L.off_b = a_bytes;
   L.off_hist = L.off_b + b_bytes;
@@ -319,20 +332,69 @@ RowLayout row_layout(const profk_plan_t& p, int dtype) {
   return L;
 }
 
-template <int DT>
+// The plan's arrays in 32-bit byte sums: the buffer alone takes 4*M bytes
+// (and a large sample 4*S).
+static bool row_sums_fit(const profk_plan_t& p, int64_t max_k) {
+  constexpr int64_t kMaxWords = kRowMaxLds / 4;
+  return p.k <= max_k && p.M <= kMaxWords && p.S <= kMaxWords;
+}
+
+bool rows_fit_block(const profk_plan_t& p, int dtype) {
+  return row_sums_fit(p, kRowMaxK) && row_layout(p, dtype, kRowBS).bytes <= kRowMaxLds;
+}
+
+// Threads per row.  A workgroup's rate is bound by the loads it has in flight
+// (measured, fp32 rows alone on a CU: 7 GB/s with 256 threads, 37 with 1024),
+// a short row's time by the latency of its stages (about 10 us, however many
+// threads), so short rows want many small workgroups per CU and long or few
+// rows large ones.  Measured on one MI355X (us, 256 / 512 / 1024 threads):
+//   64 rows of 400 KB: 45 / 28 / 24;  256 of 128 KB: 26 / 22 / 18;
+//   4096 of 256 KB (bf16): 215 / 203 / 313;  1024 of 400 KB: 90 / 83 / 105;
+//   1024 of 128 KB: 36.8 / 37.0 / 62;  4096 of 64 KB: 68 / 80 / 193;
+//   8192 of 16 KB: 74 / 118 / 304;  16 of 16 KB: 16 / - / 16.
+int rows_block_threads(const profk_plan_t& p, int dtype, int64_t B, int num_cus) {
+  auto fits = [&](int bs) {
+    return row_sums_fit(p, 4 * bs) && row_layout(p, dtype, bs).bytes <= kRowMaxLds;
+  };
+  const int64_t kb = p.N * (dtype == PROFK_F32 ? 4 : 2) / 1024;
+  if (!rows_fit_block(p, dtype)) {
+    // k above kRowMaxK, or a buffer that only the vector path holds.  That
+    // path takes about 30 us a row, one after another (a row selected
+    // without sampling 50; 80 in a block).
+    if (!fits(kRowWideBS)) return 0;
+    const bool direct = p.mode == PROFK_MODE_DIRECT;
+    const int64_t block_us = (B + num_cus - 1) / num_cus * ((direct ? 80 : 15) + kb / 37);
+    const int64_t vector_us = B * (direct ? 50 : 30 + kb / 5000);
+    if (block_us >= vector_us) return 0;
+    return B > num_cus && fits(kRowMidBS) ? kRowMidBS : kRowWideBS;
+  }
+  if (kb >= 32 && B <= num_cus && fits(kRowWideBS)) return kRowWideBS;
+  if (kb >= 128 && fits(kRowMidBS)) return kRowMidBS;
+  return kRowBS;
+}
+
+template <int DT, int BS, bool PRE>
 static hipError_t launch_rows_t(const RowCall& c) {
   const profk_plan_t& p = *c.plan;
   RowArgs ra{c.values, c.row_stride, c.D, c.k, static_cast<uint32_t>(p.k_req), static_cast<uint32_t>(p.S),
              static_cast<uint32_t>(p.t), static_cast<uint32_t>(p.M), p.mode == PROFK_MODE_DIRECT ? 1 : 0,
-             c.seed, c.out_vals, c.out_idx, c.info, c.L};
-  if (p.lexicographic) hipLaunchKernelGGL((k_rows<DT, true>), dim3(c.B), dim3(kRowBS), c.L.bytes, c.stream, ra);
-  else hipLaunchKernelGGL((k_rows<DT, false>), dim3(c.B), dim3(kRowBS), c.L.bytes, c.stream, ra);
+             c.seed, c.out_vals, c.out_idx, c.info, row_layout(p, c.dtype, BS)};
+  const uint32_t lds = ra.L.bytes;
+  if (p.lexicographic) hipLaunchKernelGGL((k_rows<DT, true, BS, PRE>), dim3(c.B), dim3(BS), lds, c.stream, ra);
+  else hipLaunchKernelGGL((k_rows<DT, false, BS, PRE>), dim3(c.B), dim3(BS), lds, c.stream, ra);
   return hipGetLastError();
+}
+
+template <int DT>
+static hipError_t launch_rows_dt(const RowCall& c) {
+  if (c.threads == kRowWideBS) return launch_rows_t<DT, kRowWideBS, true>(c);
+  if (c.threads == kRowMidBS) return launch_rows_t<DT, kRowMidBS, true>(c);
+  return launch_rows_t<DT, kRowBS, false>(c);
 }
 
 hipError_t launch_rows(const RowCall& c) {
   (void)hipGetLastError();  // report only errors of this call's launches
-  return c.dtype == PROFK_F32 ? launch_rows_t<0>(c) : launch_rows_t<1>(c);
+  return c.dtype == PROFK_F32 ? launch_rows_dt<0>(c) : launch_rows_dt<1>(c);
 }
 
 }  // namespace profk

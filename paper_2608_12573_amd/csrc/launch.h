@@ -175,7 +175,9 @@ struct BigCall {
 hipError_t launch_big(const BigCall& c);
 
 // Per-row kernel: one workgroup per row, everything in LDS.
-constexpr int kRowBS = 256;                   // threads of a row block
+constexpr int kRowBS = 256;                   // threads of a row block: short rows,
+constexpr int kRowMidBS = 512;                // long rows,
+constexpr int kRowWideBS = 1024;              // few rows or a large k (rows_block_threads)
 constexpr int kRowU = 8;                      // 16-byte loads in flight per lane
 constexpr int kRowMaxK = 4 * kRowBS;          // largest k per row
 constexpr uint32_t kRowMaxLds = 144 * 1024;   // dynamic LDS the row layout may use
@@ -186,7 +188,15 @@ struct RowLayout {
   uint32_t off_a = 0, off_b = 0, off_hist = 0, off_collect = 0, off_comp = 0, bytes = 0;
 };
 
-RowLayout row_layout(const profk_plan_t& plan, int dtype);
+RowLayout row_layout(const profk_plan_t& plan, int dtype, int bs);
+
+// Row plans a block of kRowBS threads holds: k within its collect limit and
+// the sample, buffer and refinement within its LDS budget.  Calls with these
+// need no workspace.
+bool rows_fit_block(const profk_plan_t& plan, int dtype);
+// Threads of the row blocks of a call, or 0 when no row block holds the
+// plan and the rows take the vector path.
+int rows_block_threads(const profk_plan_t& plan, int dtype, int64_t B, int num_cus);
 
 struct RowCall {
   const profk_plan_t* plan;
@@ -198,7 +208,7 @@ struct RowCall {
   void* out_vals;
   int64_t* out_idx;
   profk_info_t* info;
-  RowLayout L;
+  int threads;
   hipStream_t stream;
 };
 
