@@ -15,7 +15,7 @@ import pytest
 import paper_2608_12573_amd as pk
 import workloads
 from oracle import sae as osae
-from gpu_util import note, torch
+from gpu_util import gpu_bf16, note, torch
 
 pytestmark = pytest.mark.gpu
 
@@ -187,3 +187,47 @@ def test_sae_decode(B, d_model, d_dict, k_row):
     # the same entries in the oracle's order give the same bits
     out2 = pk.sae_decode(t.from_numpy(v32).cuda(), t.from_numpy(i64).cuda(), g["w_dec"], g["b_dec"], B)
     assert t.equal(out.view(t.int32), out2.view(t.int32))
+
+
+@pytest.mark.parametrize("B,d_model,d_dict,kind", [
+    (1, 64, 100, "spread"),           # one row, one wave's columns only in part
+    (300, 72, 1000, "spread"),        # two rows a workgroup, columns past a wave's in part
+    (4099, 40, 70, "spread"),         # sixteen rows a workgroup, more workgroups than CUs
+    (20000, 8, 200, "dense"),         # several workgroups a group, many chunks
+    (2, 64, 16384, "full"),           # a single group
+    (4096, 33, 96, "spread"),         # columns not a multiple of eight
+    (520, 64, 16384, "hot"),          # one row with more entries than are held at once
+    (600, 64, 9000, "full"),          # three neighbouring rows, too many together
+])
+def test_decode_layouts(B, d_model, d_dict, kind):
+    """Rows per workgroup, column remainders, workgroups per group, and rows
+    with too many entries, against fp64: each output is a sum of its
+    terms in fp32, so it is within (terms + 2) * 2^-24 of the sum of their
+    magnitudes.  Padding and out-of-range entries are skipped."""
+    t = torch()
+    g = np.random.default_rng(B + d_model)
+    if kind == "spread":
+        idx = g.choice(B * d_dict, min(B * d_dict // 3, 20 * B), replace=False)
+    elif kind == "dense":
+        idx = g.choice(B * d_dict, B * d_dict // 4, replace=False)
+    elif kind == "hot":
+        idx = np.concatenate([5 * d_dict + np.arange(d_dict), 400 * d_dict + np.arange(0, d_dict, 7)])
+    else:
+        idx = np.concatenate([r * d_dict + np.arange(d_dict - 2) for r in {0, 1, B // 2, B - 1}])
+    idx = g.permutation(idx).astype(np.int64)
+    idx = np.concatenate([idx, [-1, B * d_dict, -5]])
+    vals = g.standard_normal(idx.size).astype(np.float32)
+    wb = workloads.f32_to_bf16_bits(g.standard_normal((d_dict, d_model)).astype(np.float32))
+    bias = g.standard_normal(d_model).astype(np.float32)
+    note(f"decode B={B} d_model={d_model} d_dict={d_dict} K={idx.size} {kind}")
+    out = pk.sae_decode(t.from_numpy(vals).cuda(), t.from_numpy(idx).cuda(), gpu_bf16(wb).view(d_dict, d_model),
+                        t.from_numpy(bias).cuda(), B).cpu().numpy()
+    w = (wb.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    ok = (idx >= 0) & (idx < B * d_dict)
+    r, j, v = idx[ok] // d_dict, idx[ok] % d_dict, vals[ok].astype(np.float64)
+    ref = np.tile(bias.astype(np.float64), (B, 1))
+    mag = np.abs(ref)
+    np.add.at(ref, r, v[:, None] * w[j])
+    np.add.at(mag, r, np.abs(v[:, None] * w[j]))
+    terms = np.bincount(r, minlength=B)[:, None]
+    assert np.all(np.abs(out - ref) <= (terms + 2) * 2.0**-24 * mag)
