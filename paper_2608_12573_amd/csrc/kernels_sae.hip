@@ -1029,10 +1029,12 @@ hipError_t launch_sae_topk(const SaeCall& c) {
   hipError_t e = launch_sae_sample(c);
   if (e != hipSuccess) return e;
   // tau: the t-th largest of the S sampled keys (per-block top-t lists in
-  // the vector path's union space, then one block)
+  // the vector path's sample space, then one block).  That space runs up to
+  // the filter's maxima: where the vector path keeps capped lists it holds
+  // every key beside them, and the lists alone would be too short here.
   if ((e = launch_select_tau_keys(reinterpret_cast<const uint32_t*>(ws + c.L.off_skeys), static_cast<uint32_t>(p.S),
                                   static_cast<uint32_t>(p.t), reinterpret_cast<uint32_t*>(ws + L.off_union),
-                                  static_cast<size_t>(L.G_s) * L.tcap, st, c.stream)) != hipSuccess)
+                                  (L.off_blk_max - L.off_union) / 4, st, c.stream)) != hipSuccess)
     return e;
   float2* col = reinterpret_cast<float2*>(ws + c.L.off_thr);
   const uint32_t d_pad = cdiv_s(c.d_dict, kSaeFBN) * kSaeFBN;
