@@ -132,10 +132,17 @@ int profk_plan_rows(int64_t D, int64_t k, double eps, double recall,
  * (batch = 1 for profk_topk and profk_batchtopk, B for profk_topk_rows).
  * It holds the sample keys, the candidate buffer, counters and the scratch
  * of the exact fallback: O(S + M + k) bytes per vector, never O(N).  For
- * profk_topk_rows it is a token 256 bytes when the row plan fits the
- * one-workgroup row kernel, else one row's vector workspace.
+ * profk_topk_rows it is the least that is accepted: a token 256 bytes when
+ * the row plan fits a workgroup's LDS, else one row's vector workspace.
  * Returns 0 when the plan or dtype is invalid. */
 size_t profk_workspace_size(const profk_plan_t* plan, int32_t dtype, int64_t batch);
+
+/* The workspace with which profk_topk_rows runs a batch of B rows fastest:
+ * profk_workspace_size(plan, dtype, B), or one vector workspace for each row
+ * of up to 64 rows at a time (at most 1 GiB, or one) where the batch takes
+ * the vector path.  Any size from profk_workspace_size up is accepted there.
+ * Returns 0 when the plan or dtype is invalid. */
+size_t profk_rows_workspace_size(const profk_plan_t* plan, int32_t dtype, int64_t B);
 
 /* Top-k of one vector (Sec. 3).  values[N] of `dtype`; out_vals[k] (same
  * dtype), out_idx[k] int64 in [0, N).  `plan` must come from profk_plan with
@@ -179,13 +186,14 @@ int profk_topk_simple(const float* values, int64_t N, int64_t k, uint64_t seed,
  * `row_plan` comes from profk_plan_rows(D, k, ...).  info_dev is NULL or an
  * array of B reports.
  *   Plans with k <= 1024 whose sample and buffer fit one workgroup's LDS
- *   (4*max(S, M) + 4*M + 16*k bytes plus about 14 KiB, within 144 KiB) run
- *   one workgroup per row entirely in LDS; `ws` is then not used (NULL, 0
- *   are accepted).  Any other plan (wider rows, larger k) runs the vector
- *   path of profk_topk on each row in turn, on `stream`, with the same
- *   per-row sample stream and result; `ws` must then hold
- *   profk_workspace_size(row_plan, dtype, B) bytes (one row's workspace,
- *   reused by every row), else PROFK_ENULL or PROFK_EWORKSPACE. */
+ *   (4*max(S, M) + 4*M + 16*k bytes plus about 14 KiB, within 144 KiB) need
+ *   no workspace: NULL, 0 are accepted.  For any other plan `ws` must hold
+ *   profk_workspace_size(row_plan, dtype, B) bytes (one row's vector
+ *   workspace), else PROFK_ENULL or PROFK_EWORKSPACE.
+ *   Rows run in one workgroup each, entirely in LDS, or, where a row is long
+ *   and the rows are few or the buffer exceeds the LDS, on the vector path of
+ *   profk_topk, as many at a time as `ws` holds a vector workspace for, with
+ *   the same per-row sample stream and result. */
 int profk_topk_rows(const profk_plan_t* row_plan, int32_t dtype,
                     const void* values, int64_t B, int64_t D,
                     int64_t row_stride, int64_t k, uint64_t seed,

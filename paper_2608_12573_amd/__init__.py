@@ -85,6 +85,8 @@ def lib():
         L.profk_plan_rows.argtypes = [i64, i64, dbl, dbl, P(PlanOpts), P(Plan)]
         L.profk_workspace_size.argtypes = [P(Plan), i32, i64]
         L.profk_workspace_size.restype = ctypes.c_size_t
+        L.profk_rows_workspace_size.argtypes = [P(Plan), i32, i64]
+        L.profk_rows_workspace_size.restype = ctypes.c_size_t
         L.profk_topk.argtypes = [P(Plan), i32, vp, i64, i64, u64, vp, vp, vp, ctypes.c_size_t, vp, vp]
         L.profk_topk_tau.argtypes = [P(Plan), i32, vp, i64, i64, u32, vp, vp, vp, ctypes.c_size_t, vp, vp]
         L.profk_topk_simple.argtypes = [vp, i64, i64, u64, vp, vp]
@@ -192,9 +194,17 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else None
 
 
+def rows_workspace_size(p, dtype, B):
+    """profk_rows_workspace_size: the workspace topk_rows runs fastest with."""
+    return int(lib().profk_rows_workspace_size(ctypes.byref(p), dtype, B))
+
+
 def workspace(p, dtype, batch=1, device="cuda"):
+    """A workspace for one vector, or (batch > 1) for topk_rows of that many
+    rows."""
     torch = _torch()
-    return torch.empty(max(workspace_size(p, dtype, batch), 1), dtype=torch.uint8, device=device)
+    n = workspace_size(p, dtype, batch) if batch == 1 else rows_workspace_size(p, dtype, batch)
+    return torch.empty(max(n, 1), dtype=torch.uint8, device=device)
 
 
 def read_info(info_tensor):

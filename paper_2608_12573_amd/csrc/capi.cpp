@@ -59,6 +59,16 @@ int run_flat(const profk_plan_t* plan, int32_t dtype, const void* values, int64_
   return e == hipSuccess ? PROFK_OK : hip_fail(e);
 }
 
+// Rows of a batch that ws_bytes hold a vector workspace each for (0: not
+// even one); a plan with k above the one-block refinement takes one at a
+// time.
+int64_t rows_at_once(const profk::FlatLayout& L, int64_t B, size_t ws_bytes) {
+  const uint64_t n = ws_bytes / L.bytes;
+  if (L.big) return n > 0 ? 1 : 0;
+  const int64_t most = B < profk::kRowBatch ? B : profk::kRowBatch;
+  return n < static_cast<uint64_t>(most) ? static_cast<int64_t>(n) : most;
+}
+
 int check_sae_shape(const void* x, const void* w_enc, const float* b_enc, int64_t B, int64_t d_model,
                     int64_t d_dict) {
   if (!x || !w_enc || !b_enc) return PROFK_ENULL;
@@ -124,6 +134,16 @@ size_t profk_workspace_size(const profk_plan_t* plan, int32_t dtype, int64_t bat
   // envelope run the vector kernels one row after another on one workspace.
   if (batch > 1 && profk::rows_fit_block(*plan, dtype)) return 256;
   return profk::flat_layout(*plan, dtype, profk::device_cu_count()).bytes;
+}
+
+size_t profk_rows_workspace_size(const profk_plan_t* plan, int32_t dtype, int64_t B) {
+  const size_t least = profk_workspace_size(plan, dtype, B);
+  if (least == 0 || B < 2) return least;
+  const int cus = profk::device_cu_count();
+  const profk::FlatLayout L = profk::flat_layout(*plan, dtype, cus);
+  const size_t cap = profk::kRowBatchBytes > L.bytes ? static_cast<size_t>(profk::kRowBatchBytes) : L.bytes;
+  const int64_t R = rows_at_once(L, B, cap);
+  return profk::rows_block_threads(*plan, dtype, B, R, cus) == 0 ? static_cast<size_t>(R) * L.bytes : least;
 }
 
 int profk_topk(const profk_plan_t* plan, int32_t dtype, const void* values, int64_t N, int64_t k,
@@ -243,25 +263,26 @@ int profk_topk_rows(const profk_plan_t* plan, int32_t dtype, const void* values,
   if (B < 1 || B > static_cast<int64_t>(INT32_MAX) || row_stride < D) return PROFK_EINVAL;
   if (reinterpret_cast<uintptr_t>(values) % elem_size(dtype) != 0) return PROFK_EINVAL;
   const int cus = profk::device_cu_count();
-  profk::FlatLayout FL;
-  if (!profk::rows_fit_block(*plan, dtype)) {
-    if (!ws) return PROFK_ENULL;
-    FL = profk::flat_layout(*plan, dtype, cus);
-    if (ws_bytes < FL.bytes) return PROFK_EWORKSPACE;
-  }
-  const int threads = profk::rows_block_threads(*plan, dtype, B, cus);
+  const profk::FlatLayout FL = profk::flat_layout(*plan, dtype, cus);
+  const bool small = profk::rows_fit_block(*plan, dtype);
+  if (!small && !ws) return PROFK_ENULL;
+  if (!small && ws_bytes < FL.bytes) return PROFK_EWORKSPACE;
+  const int64_t R = rows_at_once(FL, B, ws ? ws_bytes : 0);
+  const int threads = profk::rows_block_threads(*plan, dtype, B, R, cus);
   if (threads == 0) {
-    // Wide rows: each row runs the vector path (sample, filter, refinement
-    // or fallback) with its own Philox stream, counter word 1 = row, in turn
-    // on `stream`, so the rows share one workspace.
+    // The vector path (sample, filter, refinement or fallback), R rows per
+    // launch on R workspaces, each row with its own Philox stream (counter
+    // word 1 = row); stream order lets the next R rows reuse them.
     const uint64_t es = elem_size(dtype);
     (void)hipGetLastError();
-    for (int64_t r = 0; r < B; ++r) {
+    for (int64_t r = 0; r < B; r += R) {
       profk::FlatCall fc{plan, dtype, static_cast<const uint8_t*>(values) + static_cast<uint64_t>(r) * row_stride * es,
                          static_cast<uint32_t>(D), static_cast<uint32_t>(k), seed, static_cast<uint64_t>(r),
                          static_cast<uint8_t*>(out_vals) + static_cast<uint64_t>(r) * k * es, out_idx + r * k,
                          static_cast<uint8_t*>(ws), FL, static_cast<hipStream_t>(stream),
                          info_dev ? info_dev + r : nullptr, 0, 0};
+      fc.rows = static_cast<uint32_t>(B - r < R ? B - r : R);
+      fc.stride = {static_cast<uint64_t>(row_stride) * es, FL.bytes};
       const hipError_t e = profk::launch_flat(fc);
       if (e != hipSuccess) return hip_fail(e);
     }

@@ -14,6 +14,7 @@
 #include "device_common.h"
 #include "filter_tile.h"
 #include "launch.h"
+#include "sample_union.h"
 
 namespace profk {
 
@@ -23,7 +24,7 @@ template <class T> static T* at(uint8_t* ws, size_t off) { return reinterpret_ca
 // ------------------------------------------------------------ stage 3 -----
 struct FilterArgs {
   const void* values;
-  uint32_t n, head, nvec;
+  uint32_t n, head, nvec;      // (a batch: head and nvec are set by select_vector)
   uint32_t seg_cap;
   CallState* st;
   const uint32_t* union_keys;  // sample union to select tau from, or null: tau in st
@@ -37,14 +38,32 @@ struct FilterArgs {
   uint32_t n_all;
   uint32_t *seg_cnt, *seg_key, *seg_idx, *blk_max;
   uint32_t* fhist;             // refinement histogram (or null), zero on entry
+  BatchStride bs;
+  template <int DT>
+  __device__ __forceinline__ void select_vector() {
+    at_vector(values, bs.val);
+    at_vector(st, bs.ws);
+    at_vector(union_keys, bs.ws);
+    at_vector(cut, bs.ws);
+    at_vector(all_keys, bs.ws);
+    at_vector(seg_cnt, bs.ws);
+    at_vector(seg_key, bs.ws);
+    at_vector(seg_idx, bs.ws);
+    at_vector(blk_max, bs.ws);
+    at_vector(fhist, bs.ws);
+    head = static_cast<uint32_t>(((16 - (reinterpret_cast<uintptr_t>(values) & 15)) & 15) / Elem<DT>::ES);
+    if (head > n) head = n;
+    nvec = (n - head) / Elem<DT>::EPV;
+  }
 };
 
 // The filter pass; the survival test is in filter_tile.h.
 // U: 16-byte loads per lane and step.  DB: the next step's loads are issued
 // before the current step is tested, which pays where most steps take the
 // survivor path and costs a little on the sparse stream of a large input.
-template <int DT, bool LEX, int U, bool DB>
+template <int DT, bool LEX, int U, bool DB, bool BATCH>
 __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
+  if constexpr (BATCH) a.select_vector<DT>();
   constexpr int EPV = Elem<DT>::EPV;
   constexpr int ES = Elem<DT>::ES;
   __shared__ uint32_t s_skey[kStage], s_sidx[kStage];
@@ -246,11 +265,22 @@ int filter_blocks_per_cu(int dtype, int want) {
   if (cached[d] == 0) {
     int n = 0;
     const hipError_t e = d == 0
-        ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_filter<0, false, kFiltUSmall, true>, kFiltBS, 0)
-        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_filter<1, false, kFiltUSmall, true>, kFiltBS, 0);
+        ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_filter<0, false, kFiltUSmall, true, false>, kFiltBS, 0)
+        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_filter<1, false, kFiltUSmall, true, false>, kFiltBS, 0);
     cached[d] = (e == hipSuccess && n > 0) ? n : kFiltPerCuDense;
   }
   return cached[d] < want ? cached[d] : want;
+}
+
+template <int DT, bool LEX, bool BATCH>
+static void launch_filter_variant(const FlatCall& c, const FilterArgs& fa) {
+  const FlatLayout& L = c.L;
+  // small inputs are never sparse: their steps are always double-buffered
+  const bool large = L.filt_u == kFiltULarge, db = L.filt_db;
+  const dim3 G(filter_grid(c), c.rows), BS(kFiltBS);
+  if (!large) hipLaunchKernelGGL((k_filter<DT, LEX, kFiltUSmall, true, BATCH>), G, BS, 0, c.stream, fa);
+  else if (db) hipLaunchKernelGGL((k_filter<DT, LEX, kFiltULarge, true, BATCH>), G, BS, 0, c.stream, fa);
+  else hipLaunchKernelGGL((k_filter<DT, LEX, kFiltULarge, false, BATCH>), G, BS, 0, c.stream, fa);
 }
 
 // union_keys null: the filter reads tau from the call state.
@@ -269,19 +299,14 @@ static hipError_t launch_filter_t(const FlatCall& c, CallState* st, const uint32
                 static_cast<uint32_t>(c.plan->S),
                 at<uint32_t>(c.ws, L.off_segcnt), at<uint32_t>(c.ws, L.off_seg_key),
                 at<uint32_t>(c.ws, L.off_seg_idx), at<uint32_t>(c.ws, L.off_blk_max),
-                at<uint32_t>(c.ws, L.off_fhist)};
+                at<uint32_t>(c.ws, L.off_fhist), c.stride};
   if (c.ev_before) (void)hipEventRecord(c.ev_before, c.stream);
-  // small inputs are never sparse: their steps are always double-buffered
-  const bool large = L.filt_u == kFiltULarge, db = L.filt_db;
-  const dim3 G(L.G_f), BS(kFiltBS);
-  if (lex) {
-    if (!large) hipLaunchKernelGGL((k_filter<DT, true, kFiltUSmall, true>), G, BS, 0, c.stream, fa);
-    else if (db) hipLaunchKernelGGL((k_filter<DT, true, kFiltULarge, true>), G, BS, 0, c.stream, fa);
-    else hipLaunchKernelGGL((k_filter<DT, true, kFiltULarge, false>), G, BS, 0, c.stream, fa);
+  if (c.rows > 1) {
+    if (lex) launch_filter_variant<DT, true, true>(c, fa);
+    else launch_filter_variant<DT, false, true>(c, fa);
   } else {
-    if (!large) hipLaunchKernelGGL((k_filter<DT, false, kFiltUSmall, true>), G, BS, 0, c.stream, fa);
-    else if (db) hipLaunchKernelGGL((k_filter<DT, false, kFiltULarge, true>), G, BS, 0, c.stream, fa);
-    else hipLaunchKernelGGL((k_filter<DT, false, kFiltULarge, false>), G, BS, 0, c.stream, fa);
+    if (lex) launch_filter_variant<DT, true, false>(c, fa);
+    else launch_filter_variant<DT, false, false>(c, fa);
   }
   if (c.ev_after) (void)hipEventRecord(c.ev_after, c.stream);
   return hipGetLastError();

@@ -42,10 +42,22 @@ struct SampleArgs {
   // draw's key at its draw number; null otherwise
   uint32_t* cut;
   uint32_t* all_keys;
+  BatchStride bs;
+  __device__ __forceinline__ void select_vector() {
+    at_vector(values, bs.val);
+    row += blockIdx.y;
+    at_vector(union_keys, bs.ws);
+    at_vector(st, bs.ws);
+    at_vector(seg_cnt, bs.ws);
+    at_vector(fhist, bs.ws);
+    at_vector(cut, bs.ws);
+    at_vector(all_keys, bs.ws);
+  }
 };
 
-template <int DT, int BS>
+template <int DT, int BS, bool BATCH>
 __global__ __launch_bounds__(BS) void k_sample(SampleArgs a) {
+  if constexpr (BATCH) a.select_vector();
   constexpr uint32_t kPer = 4 * BS;  // four draws per thread
   __shared__ SampleUnionShared<BS> sh;
   const uint32_t b = blockIdx.x, tid = threadIdx.x;
@@ -119,9 +131,17 @@ struct TauArgs {
   uint32_t n_cut;
   const uint32_t* all_keys;
   uint32_t n_all;
+  uint64_t ws_stride;  // between the vectors of a batch
 };
 
+template <bool BATCH>
 __global__ __launch_bounds__(kTauBS) void k_select_tau(TauArgs a) {
+  if constexpr (BATCH) {
+    at_vector(a.keys, a.ws_stride);
+    at_vector(a.st, a.ws_stride);
+    at_vector(a.cut, a.ws_stride);
+    at_vector(a.all_keys, a.ws_stride);
+  }
   constexpr int E = 8;  // keys per thread when the union is held in registers
   __shared__ uint32_t cache[kTauCache];
   __shared__ SelectShared sel;
@@ -253,10 +273,15 @@ struct TauIdxArgs {
   uint32_t S, t;
   CallState* st;
   uint32_t* list;  // S entries
+  BatchStride bs;
 };
 
 template <int DT>
 __global__ __launch_bounds__(kSampBS) void k_tau_index(TauIdxArgs a) {
+  at_vector(a.values, a.bs.val);
+  a.row += blockIdx.y;
+  at_vector(a.st, a.bs.ws);
+  at_vector(a.list, a.bs.ws);
   __shared__ uint32_t s_list[kSampPerBlock];
   __shared__ SelectShared sel;
   __shared__ uint32_t s_n, s_base, s_last;
@@ -319,9 +344,13 @@ struct InitArgs {
   uint32_t* bcur;   // null unless the call takes the large-k path
   uint32_t* ghist;  // null unless the call takes the large-k path
   uint32_t tau_key;
+  uint64_t ws_stride;
 };
 
 __global__ void k_init_state(InitArgs a) {
+  at_vector(a.st, a.ws_stride);
+  at_vector(a.seg_cnt, a.ws_stride);
+  at_vector(a.fhist, a.ws_stride);
   reset_state(a.st, a.seg_cnt, a.fhist, a.bcur, a.ghist);
   if (threadIdx.x == 0) a.st->tau_key = a.tau_key;
 }
@@ -554,13 +583,39 @@ struct FinishArgs {
   uint32_t G_f, seg_cap;
   const uint32_t *seg_cnt, *seg_key, *seg_idx, *blk_max;
   CallState* st;
-  uint32_t head, nvec, cv;          // fallback chunks: see ChunkSrc
+  uint32_t head, nvec, cv;          // fallback chunks: see ChunkSrc (a batch: set by select_vector)
   uint32_t *cand_key, *cand_idx;    // each chunk's top k, chunk b at b*k
   uint32_t *grp_key, *grp_idx;      // each chunk group's top k, group g at g*k
   const uint32_t* fhist;           // the filter's histogram of log_bin(key - tau)
   void* out_vals;
   int64_t* out_idx;
   profk_info_t* info;
+  BatchStride bs;
+  // Fallback chunks are whole 16-byte vectors after the unaligned head, as
+  // the filter splits the input.
+  template <int DT>
+  __device__ __forceinline__ void select_vector() {
+    constexpr uint32_t ES = Elem<DT>::ES, EPV = Elem<DT>::EPV;
+    const uint64_t y = blockIdx.y;
+    at_vector(values, bs.val);
+    at_vector(seg_cnt, bs.ws);
+    at_vector(seg_key, bs.ws);
+    at_vector(seg_idx, bs.ws);
+    at_vector(blk_max, bs.ws);
+    at_vector(st, bs.ws);
+    at_vector(cand_key, bs.ws);
+    at_vector(cand_idx, bs.ws);
+    at_vector(grp_key, bs.ws);
+    at_vector(grp_idx, bs.ws);
+    at_vector(fhist, bs.ws);
+    out_vals = static_cast<char*>(out_vals) + y * k * ES;
+    out_idx += y * k;
+    if (info) info += y;
+    head = static_cast<uint32_t>(((16 - (reinterpret_cast<uintptr_t>(values) & 15)) & 15) / ES);
+    if (head > n) head = n;
+    nvec = (n - head) / EPV;
+    cv = (nvec + gridDim.x - 1) / gridDim.x;
+  }
 };
 
 // Refinement of a filtered call (k_req <= total <= M), from the filter's
@@ -786,8 +841,9 @@ __device__ __forceinline__ void finish_filtered(const FinishArgs& a, FinLds& sh,
   }
 }
 
-template <int DT>
+template <int DT, bool BATCH>
 __global__ __launch_bounds__(kFinBS) void k_finish(FinishArgs a) {
+  if constexpr (BATCH) a.select_vector<DT>();
   __shared__ FinLds sh;
   __shared__ SelectScratch fs;
   __shared__ uint32_t seg_n[kSegs], seg_pre[kSegs + 1], flag;
@@ -1011,6 +1067,7 @@ FlatLayout flat_layout(const profk_plan_t& p, int dtype, int num_cus) {
   L.filt_db = !sparse;
   uint32_t g = cdiv(cdiv(N, epv), kFiltBS * static_cast<uint32_t>(L.filt_u));
   L.G_f = g < 1 ? 1 : (g > maxg ? maxg : g);
+  L.G_fmax = maxg;
   L.seg_cap = M;
   const uint32_t fbmax = static_cast<uint32_t>(num_cus < kFbMaxBlocks ? num_cus : kFbMaxBlocks);
   uint32_t gb = cdiv(N, kFbMinChunk);
@@ -1072,25 +1129,28 @@ static hipError_t launch_refine_t(const FlatCall& c, bool direct, uint32_t G_f) 
                L.G_big, c.out_vals, c.out_idx, c.info, c.stream};
     return launch_big(bc);
   }
-  // Fallback chunks (ChunkSrc): whole 16-byte vectors after the unaligned
-  // head, as the filter splits the input, and at least max(k, kFbMinChunk)
-  // elements each, so that every chunk but the last holds k of the top.
-  constexpr int ES = Elem<DT>::ES, EPV = Elem<DT>::EPV;
+  // Fallback chunks (ChunkSrc) hold at least max(k, kFbMinChunk) elements
+  // each, so that every chunk but the last holds k of the top, wherever the
+  // vector's first aligned element is; the vectors of a batch share the grid.
+  constexpr uint32_t ES = Elem<DT>::ES, EPV = Elem<DT>::EPV;
+  const uint64_t min_chunk = c.k > kFbMinChunk ? c.k : kFbMinChunk;
+  const uint64_t whole = c.n > 2 * EPV ? (c.n - (EPV - 1)) / EPV * EPV : 0;  // least elements in whole vectors
+  const uint64_t share = (L.G_fb + c.rows - 1) / c.rows;
+  const uint64_t gmax = whole / min_chunk < share ? whole / min_chunk : share;
+  const uint32_t G_fb = gmax < 1 ? 1u : static_cast<uint32_t>(gmax);
   const uintptr_t addr = reinterpret_cast<uintptr_t>(c.values);
   uint32_t head = static_cast<uint32_t>(((16 - (addr & 15)) & 15) / ES);
   if (head > c.n) head = c.n;
   const uint32_t nvec = (c.n - head) / EPV;
-  const uint64_t min_chunk = c.k > kFbMinChunk ? c.k : kFbMinChunk;
-  const uint64_t gmax = static_cast<uint64_t>(nvec) * EPV / min_chunk;
-  const uint32_t G_fb = gmax < 1 ? 1u : (gmax < L.G_fb ? static_cast<uint32_t>(gmax) : L.G_fb);
   FinishArgs fa{c.values, c.n, c.k, static_cast<uint32_t>(p.k_req), static_cast<uint32_t>(p.M),
                 direct ? 1 : 0, G_f, L.seg_cap,
                 seg_cnt, at<uint32_t>(c.ws, L.off_seg_key), at<uint32_t>(c.ws, L.off_seg_idx),
                 at<uint32_t>(c.ws, L.off_blk_max), st,
                 head, nvec, cdiv(nvec, G_fb), at<uint32_t>(c.ws, L.off_cand_key), at<uint32_t>(c.ws, L.off_cand_idx),
                 at<uint32_t>(c.ws, L.off_grp_key), at<uint32_t>(c.ws, L.off_grp_idx),
-                fhist, c.out_vals, c.out_idx, c.info};
-  hipLaunchKernelGGL(k_finish<DT>, dim3(G_fb), dim3(kFinBS), 0, c.stream, fa);
+                fhist, c.out_vals, c.out_idx, c.info, c.stride};
+  if (c.rows > 1) hipLaunchKernelGGL((k_finish<DT, true>), dim3(G_fb, c.rows), dim3(kFinBS), 0, c.stream, fa);
+  else hipLaunchKernelGGL((k_finish<DT, false>), dim3(G_fb), dim3(kFinBS), 0, c.stream, fa);
   return hipGetLastError();
 }
 
@@ -1108,33 +1168,40 @@ static hipError_t launch_flat_t(const FlatCall& c) {
   const uint32_t* union_for_filter = nullptr;
   hipError_t e;
   if (direct || c.use_tau) {
-    hipLaunchKernelGGL(k_init_state, dim3(1), dim3(64), 0, c.stream,
-                       InitArgs{st, seg_cnt, fhist, bcur, ghist, c.use_tau ? c.tau_key : 0u});
+    hipLaunchKernelGGL(k_init_state, dim3(1, c.rows), dim3(64), 0, c.stream,
+                       InitArgs{st, seg_cnt, fhist, bcur, ghist, c.use_tau ? c.tau_key : 0u, c.stride.ws});
   } else {
     uint32_t* uk = at<uint32_t>(c.ws, L.off_union);
     SampleArgs sa{c.values, c.n, c.seed, c.row, static_cast<uint32_t>(p.S),
                   L.cap_list ? L.cap_list : static_cast<uint32_t>(p.t), L.tcap, uk, st, seg_cnt, fhist, bcur, ghist,
                   L.cap_list ? at<uint32_t>(c.ws, L.off_cut) : nullptr,
-                  L.cap_list ? at<uint32_t>(c.ws, L.off_all_keys) : nullptr};
-    if (L.samp_bs == kSampWideBS) hipLaunchKernelGGL((k_sample<DT, kSampWideBS>), dim3(L.G_s), dim3(kSampWideBS), 0, c.stream, sa);
-    else hipLaunchKernelGGL((k_sample<DT, kSampBS>), dim3(L.G_s), dim3(kSampBS), 0, c.stream, sa);
+                  L.cap_list ? at<uint32_t>(c.ws, L.off_all_keys) : nullptr, c.stride};
+    const dim3 gs(L.G_s, c.rows);
+    if (L.samp_bs == kSampWideBS) {
+      if (c.rows > 1) hipLaunchKernelGGL((k_sample<DT, kSampWideBS, true>), gs, dim3(kSampWideBS), 0, c.stream, sa);
+      else hipLaunchKernelGGL((k_sample<DT, kSampWideBS, false>), gs, dim3(kSampWideBS), 0, c.stream, sa);
+    } else {
+      if (c.rows > 1) hipLaunchKernelGGL((k_sample<DT, kSampBS, true>), gs, dim3(kSampBS), 0, c.stream, sa);
+      else hipLaunchKernelGGL((k_sample<DT, kSampBS, false>), gs, dim3(kSampBS), 0, c.stream, sa);
+    }
     if (!lex && L.union_n <= kFiltTauMax) {
       union_for_filter = uk;
     } else {
       TauArgs ta{uk, L.union_n, static_cast<uint32_t>(p.t), Elem<DT>::KEYBITS, st,
                  L.cap_list ? at<uint32_t>(c.ws, L.off_cut) : nullptr, L.G_s,
-                 L.cap_list ? at<uint32_t>(c.ws, L.off_all_keys) : nullptr, static_cast<uint32_t>(p.S)};
-      hipLaunchKernelGGL(k_select_tau, dim3(1), dim3(kTauBS), 0, c.stream, ta);
+                 L.cap_list ? at<uint32_t>(c.ws, L.off_all_keys) : nullptr, static_cast<uint32_t>(p.S), c.stride.ws};
+      if (c.rows > 1) hipLaunchKernelGGL(k_select_tau<true>, dim3(1, c.rows), dim3(kTauBS), 0, c.stream, ta);
+      else hipLaunchKernelGGL(k_select_tau<false>, dim3(1), dim3(kTauBS), 0, c.stream, ta);
       if (lex) {
         TauIdxArgs ti{c.values, c.n, c.seed, c.row, static_cast<uint32_t>(p.S), static_cast<uint32_t>(p.t), st,
-                      at<uint32_t>(c.ws, L.off_tie)};
-        hipLaunchKernelGGL(k_tau_index<DT>, dim3(L.G_s), dim3(kSampBS), 0, c.stream, ti);
+                      at<uint32_t>(c.ws, L.off_tie), c.stride};
+        hipLaunchKernelGGL(k_tau_index<DT>, dim3(L.G_s, c.rows), dim3(kSampBS), 0, c.stream, ti);
       }
     }
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!direct && (e = launch_filter(c, st, union_for_filter, lex)) != hipSuccess) return e;
-  return launch_refine_t<DT>(c, direct, L.G_f);
+  return launch_refine_t<DT>(c, direct, filter_grid(c));
 }
 
 hipError_t launch_flat(const FlatCall& c) {
@@ -1148,8 +1215,8 @@ hipError_t launch_refine(const FlatCall& c, uint32_t G_f) {
 
 hipError_t launch_select_tau(const uint32_t* union_keys, uint32_t n, uint32_t t, int keybits, CallState* st,
                              hipStream_t s) {
-  TauArgs ta{union_keys, n, t, keybits, st};
-  hipLaunchKernelGGL(k_select_tau, dim3(1), dim3(kTauBS), 0, s, ta);
+  TauArgs ta{union_keys, n, t, keybits, st, nullptr, 0, nullptr, 0, 0};
+  hipLaunchKernelGGL(k_select_tau<false>, dim3(1), dim3(kTauBS), 0, s, ta);
   return hipGetLastError();
 }
 

@@ -352,23 +352,27 @@ bool rows_fit_block(const profk_plan_t& p, int dtype) {
 //   4096 of 256 KB (bf16): 215 / 203 / 313;  1024 of 400 KB: 90 / 83 / 105;
 //   1024 of 128 KB: 36.8 / 37.0 / 62;  4096 of 64 KB: 68 / 80 / 193;
 //   8192 of 16 KB: 74 / 118 / 304;  16 of 16 KB: 16 / - / 16.
-int rows_block_threads(const profk_plan_t& p, int dtype, int64_t B, int num_cus) {
+// The vector path (sample, filter, refinement: three launches of which each
+// takes R rows) shares every row out over the chip, which pays where a row is
+// long and the rows are few.  Measured (us, 1024 threads / vector path, k = 32
+// fp32): 4 rows of 400 KB 22 / 23, of 1 MB 37 / 23, of 4 MB 100 / 25; 64 rows
+// of 400 KB 24 / 30, of 1 MB 41 / 37, of 4 MB 119 / 72; 256 rows of 1 MB 57 / 147.
+// (one row after another, as before, 8 rows of 16 MB took 192 us, against 42.)
+int rows_block_threads(const profk_plan_t& p, int dtype, int64_t B, int64_t R, int num_cus) {
   auto fits = [&](int bs) {
     return row_sums_fit(p, 4 * bs) && row_layout(p, dtype, bs).bytes <= kRowMaxLds;
   };
   const int64_t kb = p.N * (dtype == PROFK_F32 ? 4 : 2) / 1024;
-  if (!rows_fit_block(p, dtype)) {
-    // k above kRowMaxK, or a buffer that only the vector path holds.  That
-    // path takes about 30 us a row, one after another (a row selected
-    // without sampling 50; 80 in a block).
-    if (!fits(kRowWideBS)) return 0;
+  const bool small = rows_fit_block(p, dtype), wide = fits(kRowWideBS);
+  if (!small && !wide) return 0;
+  if (wide && R > 0) {
     const bool direct = p.mode == PROFK_MODE_DIRECT;
-    const int64_t block_us = (B + num_cus - 1) / num_cus * ((direct ? 80 : 15) + kb / 37);
-    const int64_t vector_us = B * (direct ? 50 : 30 + kb / 5000);
-    if (block_us >= vector_us) return 0;
-    return B > num_cus && fits(kRowMidBS) ? kRowMidBS : kRowWideBS;
+    const int64_t block_us = (B + num_cus - 1) / num_cus * ((direct ? 80 : 12) + kb / 37);
+    const int64_t vector_us = (B + R - 1) / R * (direct ? 50 : 23) + B * kb / 5500 + B / 8;
+    if (block_us > vector_us) return 0;
   }
-  if (kb >= 32 && B <= num_cus && fits(kRowWideBS)) return kRowWideBS;
+  if (!small) return B > num_cus && fits(kRowMidBS) ? kRowMidBS : kRowWideBS;
+  if (kb >= 32 && B <= num_cus && wide) return kRowWideBS;
   if (kb >= 128 && fits(kRowMidBS)) return kRowMidBS;
   return kRowBS;
 }

@@ -98,7 +98,7 @@ struct FlatLayout {
   uint32_t samp_bs = 0;                       // threads of a sample block (four draws each)
   uint32_t cap_list = 0;                      // capped sample lists: their length, else 0
   size_t off_cut = 0, off_all_keys = 0;       // capped lists: each block's cut key, every sample key
-  uint32_t G_f = 0;                           // filter blocks
+  uint32_t G_f = 0, G_fmax = 0;               // filter blocks, and the most that are resident
   int filt_u = 0;                             // 16-byte loads per lane and filter step
   bool filt_db = true;                        // filter steps double-buffered (all but the sparse launch)
   uint32_t seg_cap = 0;                       // entries per candidate segment (= M)
@@ -118,6 +118,13 @@ struct FlatLayout {
 
 FlatLayout flat_layout(const profk_plan_t& plan, int dtype, int num_cus);
 
+// A batch of vectors of one plan: blockIdx.y = vector y, whose values start
+// val bytes after the one before it and whose workspace ws bytes after; its
+// outputs follow the k of the one before.
+struct BatchStride {
+  uint64_t val = 0, ws = 0;
+};
+
 struct FlatCall {
   const profk_plan_t* plan;
   int dtype;
@@ -134,7 +141,16 @@ struct FlatCall {
   int use_tau;          // 1: threshold given by the caller
   uint32_t tau_key;
   hipEvent_t ev_before = nullptr, ev_after = nullptr;  // around the filter launch
+  uint32_t rows = 1;    // vectors of the call (1 where L.big)
+  BatchStride stride;   // between them
 };
+
+// Filter workgroups of each vector of the call: the vectors of a batch share
+// the largest grid.
+inline uint32_t filter_grid(const FlatCall& c) {
+  const uint32_t share = (c.L.G_fmax + c.rows - 1) / c.rows;
+  return c.L.G_f < share ? c.L.G_f : share;
+}
 
 hipError_t launch_flat(const FlatCall& c);
 // The filter pass of c into the workspace's candidate segments; tau from
@@ -194,9 +210,12 @@ RowLayout row_layout(const profk_plan_t& plan, int dtype, int bs);
 // the sample, buffer and refinement within its LDS budget.  Calls with these
 // need no workspace.
 bool rows_fit_block(const profk_plan_t& plan, int dtype);
-// Threads of the row blocks of a call, or 0 when no row block holds the
-// plan and the rows take the vector path.
-int rows_block_threads(const profk_plan_t& plan, int dtype, int64_t B, int num_cus);
+// Threads of the row blocks of a call, or 0 when the rows take the vector
+// path, R of them at a time (R = 0: no workspace for it).
+int rows_block_threads(const profk_plan_t& plan, int dtype, int64_t B, int64_t R, int num_cus);
+// Rows the vector path takes at a time when the workspace is its choice.
+constexpr int64_t kRowBatch = 64;
+constexpr uint64_t kRowBatchBytes = 1ull << 30;
 
 struct RowCall {
   const profk_plan_t* plan;

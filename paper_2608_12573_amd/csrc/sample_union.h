@@ -10,6 +10,12 @@
 
 namespace profk {
 
+// Vector y of a batch: a workspace pointer (null stays null), the values.
+template <class T>
+__device__ __forceinline__ void at_vector(T*& p, uint64_t bytes) {
+  if (p) p = reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p) + bytes * blockIdx.y);
+}
+
 // Clears the per-call counters; fhist (kLogBins words, or null) is the
 // refinement histogram the filter accumulates into.
 // (bcur: the large-k path's bucket fill counters, one per kBktPad words, and
