@@ -409,30 +409,29 @@ __device__ __forceinline__ SelectResult block_select_kth(Visit visit, uint32_t k
 
 // The kk-th largest (1-based, with multiplicity) of m keys held in LDS, for
 // short lists: each key counts the keys above it and equal to it (m^2
-// compares in all, eight LDS reads in flight per step), and the keys with
+// compares in all, sixteen keys read per step), and the keys with
 // #above < kk <= #above + #equal, all equal to the answer, write out[0] =
-// the key and out[1] = #above.  Requires 1 <= kk <= m; every thread of the
-// block calls it, and the caller syncs before reading out.
-constexpr uint32_t kListRankMax = 256;
+// the key and out[1] = #above.  Requires 1 <= kk <= m, and a list that is
+// 16-byte aligned and zero from m to the next multiple of 16 (a zero counts
+// only as equal to a key of 0, the lowest, whose rank it cannot change).
+// Every thread of the block calls it, and the caller syncs before reading out.
+constexpr uint32_t kListRankMax = 240;
+constexpr uint32_t kListWords = kListRankMax + 16;
 template <int BS>
 __device__ __forceinline__ void list_kth(const uint32_t* list, uint32_t m, uint32_t kk, uint32_t* out) {
+  const uint4* const l4 = reinterpret_cast<const uint4*>(list);
   for (uint32_t i = threadIdx.x; i < m; i += BS) {
     const uint32_t c = list[i];
-    uint32_t gt = 0, ge = 0, j = 0;
-    for (; j + 8 <= m; j += 8) {
-      uint32_t v[8];
+    uint32_t gt = 0, ge = 0;
+    for (uint32_t j = 0; j < m; j += 16) {
+      uint4 v[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = list[j + u];
+      for (int u = 0; u < 4; ++u) v[u] = l4[j / 4 + u];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        gt += v[u] > c ? 1u : 0u;
-        ge += v[u] >= c ? 1u : 0u;
+      for (int u = 0; u < 4; ++u) {
+        gt += (v[u].x > c ? 1u : 0u) + (v[u].y > c ? 1u : 0u) + (v[u].z > c ? 1u : 0u) + (v[u].w > c ? 1u : 0u);
+        ge += (v[u].x >= c ? 1u : 0u) + (v[u].y >= c ? 1u : 0u) + (v[u].z >= c ? 1u : 0u) + (v[u].w >= c ? 1u : 0u);
       }
-    }
-    for (; j < m; ++j) {
-      const uint32_t v = list[j];
-      gt += v > c ? 1u : 0u;
-      ge += v >= c ? 1u : 0u;
     }
     if (gt < kk && kk <= ge) {
       out[0] = c;
@@ -496,42 +495,112 @@ __device__ __forceinline__ uint32_t tau_pair_index(Draws draws, uint32_t tau, ui
   return ~res.kth;
 }
 
+// Appends the keys of the lanes' set mask bits to an LDS list of cap words
+// (one atomic per wave on *count; keys past cap are counted and dropped).
+template <int E>
+__device__ __forceinline__ void list_append(const uint32_t (&kv)[E], uint32_t m, uint32_t* list, uint32_t cap,
+                                            uint32_t* count) {
+  const uint32_t c = static_cast<uint32_t>(__popc(m)), incl = wave_incl_sum(c);
+  const uint32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
+  if (tot == 0) return;
+  uint32_t slot = 0;
+  if ((threadIdx.x & (kWave - 1)) == 0) slot = atomicAdd(count, tot);
+  slot = __builtin_amdgcn_readlane(slot, 0) + incl - c;
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if ((m >> e) & 1u) {
+      if (slot < cap) list[slot] = kv[e];
+      ++slot;
+    }
+}
+
 // The kk-th largest (1-based, with multiplicity) of the keys the threads of a
-// block hold in registers (E per thread, `valid` bits mark which): .x the
-// key, .y the number of keys above it.  Requires 1 <= kk <= #keys.
-// `hist` is 2^DIGIT words of LDS (16-byte aligned), `list` kListRankMax
-// words, `red` 2*BS/64 + 2 words; all may be reused once it returns (it ends
-// with a barrier).
+// block hold in registers (E per thread, `valid` bits mark which; the threads
+// from `active` on hold none): .x the key, .y the number of keys above it.
+// Requires 1 <= kk <= #keys.  `hist` is 2^DIGIT words of LDS, `list`
+// kListWords and `red` kKthRed, all 16-byte aligned; all may be reused once it
+// returns (it ends with a barrier).
 //
-// The keys' distances from their minimum are histogrammed by their leading
-// DIGIT bits, so that the bins resolve the range the keys span and not the
-// whole key range; the bin of rank kk then holds few keys, which are ranked
-// by counting.  A bin that holds more is split again, down to one key wide.
-// What bounds it is latency: six barriers and a few hundred LDS reads,
-// whatever kk.  Taking a wave-wide maximum per rank instead (in every wave,
-// then over the waves' lists) cost about 420 cycles per rank, twice: 15800
-// cycles for the 22nd of 382 keys on 256 threads, against 6000 here.
+// A small kk on up to 512 threads: the kk-th largest of the maxima of the
+// 16-lane groups is at most the answer, and few keys reach it (about ten for
+// kk = 7 of 1024), which are ranked by counting.  It takes an eighth more
+// groups that hold keys than kk.
+// Otherwise (also when ties make those many): the keys' distances from their
+// minimum are histogrammed by their leading DIGIT bits, so that the bins
+// resolve the range the keys span and not the whole key range, and the few
+// keys in the bin of rank kk are ranked by counting.  A bin that holds more is
+// split again, down to one key wide.
+//
+// What bounds it is latency: three barriers and about 2500 cycles by groups,
+// six and about 5500 by the histogram (smaller groups, up to 64 of them, for
+// larger kk were slower: 8192 rows with 22 of 382 keys each 72 -> 81 us).
+// Taking a wave-wide maximum per rank instead (in every wave, then over the
+// waves' lists) cost about 420 cycles per rank, twice: 15800 cycles for the
+// 22nd of 382 keys on 256 threads.
+constexpr uint32_t kKthLanes = 16;
+constexpr uint32_t kKthGroups = 32;  // most groups
+constexpr uint32_t kKthRed = kKthGroups + 4;
 template <int BS, int E, int DIGIT>
-__device__ __forceinline__ uint2 block_kth_regs(const uint32_t (&kv)[E], uint32_t valid, uint32_t kk,
+__device__ __forceinline__ uint2 block_kth_regs(const uint32_t (&kv)[E], uint32_t valid, uint32_t active, uint32_t kk,
                                                 uint32_t* hist, uint32_t* list, uint32_t* red,
                                                 SelectScratch& sc) {
   constexpr int NW = BS / kWave;
   constexpr uint32_t NB = 1u << DIGIT;
+  static_assert(2 * NW <= static_cast<int>(kKthGroups), "red");
+  constexpr uint32_t NG = BS / kKthLanes;
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  uint32_t mx = 0, nmn = 0;  // largest key, complement of the smallest
+  uint32_t* const count = red + kKthGroups;
+  uint32_t mx = 0;
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const bool in = (valid >> e) & 1u;
-    mx = max(mx, in ? kv[e] : 0u);
-    nmn = max(nmn, in ? ~kv[e] : 0u);
+  for (int e = 0; e < E; ++e) mx = max(mx, ((valid >> e) & 1u) ? kv[e] : 0u);
+  for (uint32_t i = tid; i < kListWords; i += BS) list[i] = 0;
+  if (tid == 0) *count = 0;
+  if (NG <= kKthGroups && active >= (kk + kk / 8) * kKthLanes) {
+    uint32_t g = mx;
+    g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0xB1, 0xF, 0xF, false)));
+    g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x4E, 0xF, 0xF, false)));
+    g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x141, 0xF, 0xF, false)));
+    g = max(g, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(g), 0x140, 0xF, 0xF, false)));
+    if (lane % kKthLanes == 0) red[tid / kKthLanes] = g;
+    __syncthreads();
+    // every wave: the kk-th largest of the NG >= kk maxima (those of groups
+    // without keys are 0)
+    const uint32_t c = lane < NG ? red[lane] : 0u;
+    uint32_t gt = 0, ge = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < NG; j += 4) {
+      const uint4 v = reinterpret_cast<const uint4*>(red)[j / 4];
+      gt += (v.x > c ? 1u : 0u) + (v.y > c ? 1u : 0u) + (v.z > c ? 1u : 0u) + (v.w > c ? 1u : 0u);
+      ge += (v.x >= c ? 1u : 0u) + (v.y >= c ? 1u : 0u) + (v.z >= c ? 1u : 0u) + (v.w >= c ? 1u : 0u);
+    }
+    const uint64_t at = __ballot(lane < NG && gt < kk && kk <= ge);
+    const uint32_t low = __builtin_amdgcn_readlane(c, __ffsll(static_cast<unsigned long long>(at)) - 1);
+    uint32_t m = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) m |= (kv[e] >= low ? 1u : 0u) << e;
+    list_append<E>(kv, m & valid, list, kListRankMax, count);
+    __syncthreads();
+    const uint32_t n = *count;
+    if (n <= kListRankMax) {
+      list_kth<BS>(list, n, kk, sc.found);
+      __syncthreads();
+      const uint2 r{sc.found[0], sc.found[1]};
+      __syncthreads();
+      return r;
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < kListWords; i += BS) list[i] = 0;
+    if (tid == 0) *count = 0;
   }
+  uint32_t nmn = 0;  // complement of the smallest key
+#pragma unroll
+  for (int e = 0; e < E; ++e) nmn = max(nmn, ((valid >> e) & 1u) ? ~kv[e] : 0u);
   mx = wave_max_u32(mx);
   nmn = wave_max_u32(nmn);
   if (lane == 0) {
     red[w] = mx;
     red[NW + w] = nmn;
   }
-  if (tid == 0) red[2 * NW] = 0;  // entries of `list`
   for (uint32_t b = tid; b < NB; b += BS) hist[b] = 0;
   __syncthreads();
 #pragma unroll
@@ -561,18 +630,8 @@ __device__ __forceinline__ uint2 block_kth_regs(const uint32_t (&kv)[E], uint32_
     if (eq <= kListRankMax) {
       uint32_t m = 0;
 #pragma unroll
-      for (int e = 0; e < E; ++e)
-        m |= (((valid >> e) & 1u) && kv[e] >= base && ((kv[e] - base) >> shift) == 0 ? 1u : 0u) << e;
-      const uint32_t c = static_cast<uint32_t>(__popc(m)), incl = wave_incl_sum(c);
-      const uint32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
-      if (tot) {
-        uint32_t slot = 0;
-        if (lane == 0) slot = atomicAdd(&red[2 * NW], tot);
-        slot = __builtin_amdgcn_readlane(slot, 0) + incl - c;
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-          if ((m >> e) & 1u) list[slot++] = kv[e];
-      }
+      for (int e = 0; e < E; ++e) m |= (((kv[e] - base) >> shift) == 0 ? 1u : 0u) << e;
+      list_append<E>(kv, m & valid, list, kListRankMax, count);
       __syncthreads();
       list_kth<BS>(list, eq, krem, sc.found);
       __syncthreads();

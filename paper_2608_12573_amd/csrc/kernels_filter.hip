@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
   // histogram of its survivors
   __shared__ __align__(16) uint32_t s_pool[kLogBins];
   constexpr int kTauDigit = 10;
-  static_assert((1u << kTauDigit) + kListRankMax <= kLogBins, "select of tau");
-  __shared__ uint32_t s_red[2 * (kFiltBS / kWave) + 2];
+  static_assert((1u << kTauDigit) + kListWords <= kLogBins, "select of tau");
+  __shared__ __align__(16) uint32_t s_red[kKthRed];
   __shared__ SelectScratch s_sc;
   __shared__ uint32_t s_cnt, s_base;
   __shared__ uint32_t s_wmax[kFiltBS / kWave];
@@ -126,7 +126,9 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
   // ---- threshold (stage 2) when the sample union is small
   uint32_t tau;
   if (a.union_n) {
-    tau = block_kth_regs<kFiltBS, E, kTauDigit>(uk, valid, a.t, s_pool, s_pool + (1u << kTauDigit), s_red, s_sc).x;
+    tau = block_kth_regs<kFiltBS, E, kTauDigit>(uk, valid, min(a.union_n, static_cast<uint32_t>(kFiltBS)), a.t, s_pool,
+                                                  s_pool + (1u << kTauDigit), s_red, s_sc)
+              .x;
     if (a.all_keys)
       for (uint32_t i = tid + kFiltBS; i < a.n_cut; i += kFiltBS) cutv = max(cutv, a.cut[i]);
     if (a.all_keys && tau <= block_max<kFiltBS>(cutv, s_sc.wsum)) {

@@ -146,8 +146,8 @@ __global__ __launch_bounds__(kTauBS) void k_select_tau(TauArgs a) {
   __shared__ uint32_t cache[kTauCache];
   __shared__ SelectShared sel;
   __shared__ uint32_t list_n[2];
-  __shared__ uint32_t tlist[kTauList];
-  __shared__ uint32_t red[2 * (kTauBS / kWave) + 2];
+  __shared__ __align__(16) uint32_t tlist[kTauList];
+  __shared__ __align__(16) uint32_t red[kKthRed];
   const uint32_t tid = threadIdx.x;
   // A union of at most 8*kTauBS keys is selected from registers; larger ones
   // by digit passes over LDS or memory.
@@ -169,7 +169,9 @@ __global__ __launch_bounds__(kTauBS) void k_select_tau(TauArgs a) {
     }
     if (a.cut)
       for (uint32_t i = tid; i < a.n_cut; i += kTauBS) c = max(c, a.cut[i]);
-    const uint32_t kth = block_kth_regs<kTauBS, E, kSelDigit>(v, valid, a.t, sel.hist, tlist, red, sel.scratch()).x;
+    const uint32_t kth = block_kth_regs<kTauBS, E, kSelDigit>(v, valid, min(n, static_cast<uint32_t>(kTauBS)), a.t, sel.hist, tlist,
+                                                                 red, sel.scratch())
+                             .x;
     if (!a.cut || kth > block_max<kTauBS>(c, sel.wsum)) {
       if (tid == 0) a.st->tau_key = kth;
       return;
@@ -236,6 +238,7 @@ __global__ __launch_bounds__(kTauBS) void k_select_tau(TauArgs a) {
     const uint32_t d = sel.found[0], above = sel.found[1], eq = sel.found[2];
     if (eq <= kTauList) {
       if (tid == 0) list_n[0] = 0;
+      for (uint32_t i = tid; i < kListWords; i += kTauBS) tlist[i] = 0;
       __syncthreads();
       all([&](uint32_t v) {
         const bool take = ((v >> shift) & (kSelBins - 1)) == d;

@@ -63,7 +63,8 @@ __global__ __launch_bounds__(BS) void k_rows(RowArgs a) {
   uint64_t* const comp = reinterpret_cast<uint64_t*>(smem + a.L.off_comp);
   uint64_t* const exch = reinterpret_cast<uint64_t*>(smem + a.L.off_a);      // after the buffer is done
   __shared__ SelectScratch scr;
-  __shared__ uint32_t s_cnt, s_counter, s_tie_n, s_wmax[NW], s_red[2 * NW + 2];
+  __shared__ uint32_t s_cnt, s_counter, s_tie_n, s_wmax[NW];
+  __shared__ __align__(16) uint32_t s_red[kKthRed];
 
   const uint32_t r = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   const char* row = static_cast<const char*>(a.values) + static_cast<size_t>(r) * a.row_stride * ES;
@@ -125,7 +126,10 @@ __global__ __launch_bounds__(BS) void k_rows(RowArgs a) {
     if (tid == 0) s_cnt = 0;
     // 2. threshold
     if (fast) {
-      tau = block_kth_regs<BS, 8, kTauDigit>(keys, valid, a.t, hist, reinterpret_cast<uint32_t*>(comp), s_red, scr).x;
+      static_assert(kFastBucket * 8 >= kListWords * 4, "the list in comp");
+      tau = block_kth_regs<BS, 8, kTauDigit>(keys, valid, min((a.S + 3) / 4, static_cast<uint32_t>(BS)), a.t, hist,
+                                             reinterpret_cast<uint32_t*>(comp), s_red, scr)
+                .x;
     } else {
       __syncthreads();
       tau = block_select_kth<BS, kSelDigitRow>(

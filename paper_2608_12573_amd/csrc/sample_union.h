@@ -46,8 +46,8 @@ template <int BS>
 struct SampleUnionShared {
   static constexpr int kDigit = BS <= kSampBS ? 10 : 11;  // about a bin per draw, half a bin on wide blocks
   alignas(16) uint32_t hist[1 << kDigit];
-  uint32_t bin_list[kListRankMax];  // the keys of the bin holding rank t
-  uint32_t red[2 * (BS / kWave) + 2];
+  alignas(16) uint32_t list[kListWords];
+  alignas(16) uint32_t red[kKthRed];
   SelectScratch sc;
   uint32_t emitted;
 };
@@ -69,7 +69,8 @@ __device__ __forceinline__ void sample_block_top(uint32_t (&kv)[4], uint32_t val
     return;
   }
   if (tid == 0) sh.emitted = 0;  // (the select's barriers order it)
-  const uint2 r = block_kth_regs<BS, 4, SampleUnionShared<BS>::kDigit>(kv, valid, t, sh.hist, sh.bin_list, sh.red, sh.sc);
+  const uint2 r = block_kth_regs<BS, 4, SampleUnionShared<BS>::kDigit>(kv, valid, (nb + 3) / 4, t, sh.hist, sh.list,
+                                                                               sh.red, sh.sc);
   // the keys above the t-th, then copies of it up to t
   uint32_t m = 0;
 #pragma unroll
