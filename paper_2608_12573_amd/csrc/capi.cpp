@@ -267,13 +267,15 @@ int profk_topk_rows(const profk_plan_t* plan, int32_t dtype, const void* values,
   const bool small = profk::rows_fit_block(*plan, dtype);
   if (!small && !ws) return PROFK_ENULL;
   if (!small && ws_bytes < FL.bytes) return PROFK_EWORKSPACE;
-  const int64_t R = rows_at_once(FL, B, ws ? ws_bytes : 0);
+  int64_t R = rows_at_once(FL, B, ws ? ws_bytes : 0);
   const int threads = profk::rows_block_threads(*plan, dtype, B, R, cus);
-  if (threads == 0) {
+  if (threads <= 0) {
     // The vector path (sample, filter, refinement or fallback), R rows per
     // launch on R workspaces, each row with its own Philox stream (counter
-    // word 1 = row); stream order lets the next R rows reuse them.
+    // word 1 = row); stream order lets the next R rows reuse them
+    // (launch_small needs no workspace and takes every row in one launch).
     const uint64_t es = elem_size(dtype);
+    if (threads == profk::kRowsSmall) R = B;
     (void)hipGetLastError();
     for (int64_t r = 0; r < B; r += R) {
       profk::FlatCall fc{plan, dtype, static_cast<const uint8_t*>(values) + static_cast<uint64_t>(r) * row_stride * es,

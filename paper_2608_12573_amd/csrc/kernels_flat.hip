@@ -1164,6 +1164,7 @@ static hipError_t launch_flat_t(const FlatCall& c) {
   CallState* st = at<CallState>(c.ws, L.off_state);
   uint32_t* seg_cnt = at<uint32_t>(c.ws, L.off_segcnt);
   const bool direct = p.mode == PROFK_MODE_DIRECT && !c.use_tau;
+  if (direct && small_fits(c.n, c.k, DT)) return launch_small(c);
   const bool lex = p.lexicographic && !direct && !c.use_tau;  // a caller's tau: the key rule
   uint32_t* fhist = at<uint32_t>(c.ws, L.off_fhist);
   uint32_t* bcur = L.big ? at<uint32_t>(c.ws, L.off_bcur) : nullptr;

@@ -367,6 +367,7 @@ int rows_block_threads(const profk_plan_t& p, int dtype, int64_t B, int64_t R, i
     return row_sums_fit(p, 4 * bs) && row_layout(p, dtype, bs).bytes <= kRowMaxLds;
   };
   const int64_t kb = p.N * (dtype == PROFK_F32 ? 4 : 2) / 1024;
+  if (p.mode == PROFK_MODE_DIRECT && small_fits(p.N, p.k, dtype) && (kb >= kRowSmallKb || B <= num_cus)) return kRowsSmall;
   const bool small = rows_fit_block(p, dtype), wide = fits(kRowWideBS);
   if (!small && !wide) return 0;
   if (wide && R > 0) {

@@ -153,6 +153,9 @@ inline uint32_t filter_grid(const FlatCall& c) {
 }
 
 hipError_t launch_flat(const FlatCall& c);
+// A vector selected without sampling that one workgroup holds in registers.
+bool small_fits(int64_t n, int64_t k, int dtype);
+hipError_t launch_small(const FlatCall& c);
 // The filter pass of c into the workspace's candidate segments; tau from
 // the sample union when union_keys is given, else from st.
 hipError_t launch_filter(const FlatCall& c, CallState* st, const uint32_t* union_keys, bool lex);
@@ -210,8 +213,11 @@ RowLayout row_layout(const profk_plan_t& plan, int dtype, int bs);
 // the sample, buffer and refinement within its LDS budget.  Calls with these
 // need no workspace.
 bool rows_fit_block(const profk_plan_t& plan, int dtype);
-// Threads of the row blocks of a call, or 0 when the rows take the vector
-// path, R of them at a time (R = 0: no workspace for it).
+// Threads of the row blocks of a call, 0 when the rows take the vector path,
+// R of them at a time (R = 0: no workspace for it), or kRowsSmall when each
+// row is selected without sampling by launch_small's workgroup.
+constexpr int kRowsSmall = -1;
+constexpr int64_t kRowSmallKb = 16;           // shortest row of a large batch it takes
 int rows_block_threads(const profk_plan_t& plan, int dtype, int64_t B, int64_t R, int num_cus);
 // Rows the vector path takes at a time when the workspace is its choice.
 constexpr int64_t kRowBatch = 64;
