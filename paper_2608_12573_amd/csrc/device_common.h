@@ -519,7 +519,7 @@ __device__ __forceinline__ void list_append(const uint32_t (&kv)[E], uint32_t m,
 // from `active` on hold none): .x the key, .y the number of keys above it.
 // Requires 1 <= kk <= #keys.  `hist` is 2^DIGIT words of LDS, `list`
 // kListWords and `red` kKthRed, all 16-byte aligned; all may be reused once it
-// returns (it ends with a barrier).
+// returns (it ends with a barrier).  DISTINCT: no two keys are equal.
 //
 // A small kk on up to 512 threads: the kk-th largest of the maxima of the
 // 16-lane groups is at most the answer, and few keys reach it (about ten for
@@ -540,7 +540,7 @@ __device__ __forceinline__ void list_append(const uint32_t (&kv)[E], uint32_t m,
 constexpr uint32_t kKthLanes = 16;
 constexpr uint32_t kKthGroups = 32;  // most groups
 constexpr uint32_t kKthRed = kKthGroups + 4;
-template <int BS, int E, int DIGIT>
+template <int BS, int E, int DIGIT, bool DISTINCT = false>
 __device__ __forceinline__ uint2 block_kth_regs(const uint32_t (&kv)[E], uint32_t valid, uint32_t active, uint32_t kk,
                                                 uint32_t* hist, uint32_t* list, uint32_t* red,
                                                 SelectScratch& sc) {
@@ -609,14 +609,23 @@ __device__ __forceinline__ uint2 block_kth_regs(const uint32_t (&kv)[E], uint32_
     nmn = max(nmn, red[NW + i]);
   }
   uint32_t base = ~nmn, krem = kk, above = 0;
-  int wb = mx == base ? 0 : 32 - __clz(mx - base);  // the window is [base, base + 2^wb)
+  if (mx == base) {  // one key (a bucket of ties)
+    __syncthreads();
+    return uint2{base, 0u};
+  }
+  int wb = 32 - __clz(mx - base);  // the window is [base, base + 2^wb)
   while (true) {
     const int shift = wb > DIGIT ? wb - DIGIT : 0;
     const uint32_t span = wb >= 32 ? 0xFFFFFFFFu : (1u << wb) - 1u;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const uint32_t d = kv[e] - base;  // (keys below base wrap past the window or are tested by it)
-      hist_add(hist, d >> shift, ((valid >> e) & 1u) && kv[e] >= base && d <= span);
+      const bool in = ((valid >> e) & 1u) && kv[e] >= base && d <= span;
+      if (DISTINCT) {
+        if (in) atomicAdd(&hist[d >> shift], 1u);
+      } else {
+        hist_add(hist, d >> shift, in);
+      }
     }
     __syncthreads();
     if (w == 0) rank_bin_search(hist, NB, krem, sc);

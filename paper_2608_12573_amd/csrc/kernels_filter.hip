@@ -196,7 +196,12 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
       for (int u = 0; u < U; ++u) cur[u] = v[u];
       load_step(vb + vstride, th.neutral);
     } else {
-      if (vb != vbeg) load_step(vb, th.neutral);
+      // (without branches, as the first step: with them the compiler is free
+      // to wait for one load before the next, and did for bf16)
+      if (vb != vbeg) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(vec + min(vb + u * kFiltBS + tid, vend - 1));
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) cur[u] = v[u];
     }

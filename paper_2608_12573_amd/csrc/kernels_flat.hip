@@ -621,6 +621,65 @@ struct FinishArgs {
   }
 };
 
+// Exact top-kk of n <= kFinRegs*kFinBS candidates held in registers, left as
+// composites (unsorted) in g.sortbuf[0..kk).  `above` of them lie in buckets
+// above bucket bstar, which holds rank kk: the (kk - above)-th largest key of
+// that bucket and then, among its ties when only some are taken, the largest
+// ~index that is.  What it takes is the candidates' two loads and the passes
+// of 1024 threads over their registers.  Copying the candidates to LDS and
+// taking digit passes over them there took 29 us for 10256 of them with 10^4
+// tied at rank kk, half of it for the passes over the tied indices.
+constexpr int kFinRegs = 14;
+__device__ __forceinline__ void select_in_regs(const SegSrc& src, uint32_t n, uint32_t kk, uint32_t tau,
+                                               uint32_t bstar, uint32_t above, FinShared& g, SelectScratch& fs) {
+  const uint32_t tid = threadIdx.x;
+  uint32_t key[kFinRegs], nidx[kFinRegs];
+  uint32_t in_b = 0, take = 0;
+  // bucket bstar is [lo, lo + width], the buckets above it follow
+  const uint32_t lo = tau + log_bin_edge(bstar);
+  const uint32_t width = bstar + 1 < kLogBins ? log_bin_edge(bstar + 1) - log_bin_edge(bstar) - 1 : 0xFFFFFFFFu;
+#pragma unroll
+  for (int e = 0; e < kFinRegs; ++e) {
+    const uint32_t i = e * kFinBS + tid;
+    const uint2 q = src.pair_at(min(i, n - 1));
+    key[e] = q.x;
+    nidx[e] = ~q.y;
+    if (i < n && q.x >= lo) {
+      if (q.x - lo <= width) in_b |= 1u << e;
+      else take |= 1u << e;
+    }
+  }
+  uint32_t* const hist = g.cache;
+  uint32_t* const list = g.cache + (1 << kSelDigit);
+  uint32_t* const red = list + kListWords;
+  const uint2 r = block_kth_regs<kFinBS, kFinRegs, kSelDigit>(key, in_b, kFinBS, kk - above, hist, list, red, fs);
+  uint32_t ties = 0, more = 0;
+#pragma unroll
+  for (int e = 0; e < kFinRegs; ++e) {
+    ties |= (key[e] == r.x ? 1u : 0u) << e;
+    more |= (key[e] > r.x ? 1u : 0u) << e;
+  }
+  ties &= in_b;
+  take |= more & in_b;
+  const uint32_t krem = kk - above - r.y;
+  const uint32_t n_ties = block_sum<kFinBS>(static_cast<uint32_t>(__popc(ties)), fs.wsum);
+  uint32_t least = 0;
+  if (krem < n_ties) least = block_kth_regs<kFinBS, kFinRegs, kSelDigit, true>(nidx, ties, kFinBS, krem, hist, list, red, fs).x;
+  if (tid == 0) g.misc[0] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kFinRegs; ++e) take |= (((ties >> e) & 1u) && nidx[e] >= least ? 1u : 0u) << e;
+  const uint32_t c = static_cast<uint32_t>(__popc(take)), incl = wave_incl_sum(c);
+  const uint32_t tot = __builtin_amdgcn_readlane(incl, kWave - 1);
+  uint32_t slot = 0;
+  if ((tid & (kWave - 1)) == 0 && tot) slot = atomicAdd(&g.misc[0], tot);
+  slot = __builtin_amdgcn_readlane(slot, 0) + incl - c;
+#pragma unroll
+  for (int e = 0; e < kFinRegs; ++e)
+    if ((take >> e) & 1u) g.sortbuf[slot++] = (static_cast<uint64_t>(key[e]) << 32) | nidx[e];
+  __syncthreads();
+}
+
 // Refinement of a filtered call (k_req <= total <= M), from the filter's
 // histogram of log_bin(key - tau) over the candidates:
 //   1. find the bucket b* holding rank kk;
@@ -825,11 +884,16 @@ __device__ __forceinline__ void finish_filtered(const FinishArgs& a, FinLds& sh,
       }
   } else {
     if (b != 0) return;
-    __syncthreads();
-    uint32_t bm = 0;
-    for (uint32_t i = tid; i < a.G_f; i += kFinBS) bm = max(bm, a.blk_max[i]);
-    const uint32_t gmax = block_max<kFinBS>(bm, fs.wsum);
-    block_topk<kFinBS, kFinDigit>(src, total, kk, tau, max(gmax, tau), KB, sh.gen.topk());
+    const uint32_t above_b = fs.found[1];
+    __syncthreads();  // the bucket arrays are read; the selection reuses their LDS
+    if (total <= kFinRegs * kFinBS) {
+      select_in_regs(src, total, kk, tau, bstar, above_b, sh.gen, fs);
+    } else {
+      uint32_t bm = 0;
+      for (uint32_t i = tid; i < a.G_f; i += kFinBS) bm = max(bm, a.blk_max[i]);
+      const uint32_t gmax = block_max<kFinBS>(bm, fs.wsum);
+      block_topk<kFinBS, kFinDigit>(src, total, kk, tau, max(gmax, tau), KB, sh.gen.topk());
+    }
     sort_write_any<DT, kFinBS>(sh.gen.sortbuf, kk, a.k, reinterpret_cast<uint64_t*>(sh.gen.cache),
                                a.out_vals, a.out_idx);
   }

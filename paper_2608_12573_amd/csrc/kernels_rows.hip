@@ -49,7 +49,7 @@ __global__ __launch_bounds__(BS) void k_rows(RowArgs a) {
   constexpr int ES = Elem<DT>::ES, EPV = Elem<DT>::EPV, KB = Elem<DT>::KEYBITS;
   constexpr int kSelDigitRow = KB == 16 ? 8 : 11;  // sample select: 2 or 3 passes
   constexpr int kDigit = row_digit<DT>();
-  constexpr int kTauDigit = KB == 16 ? 8 : 10;         // the sample's histogram, within `hist`
+  constexpr int kTauDigit = 10;                        // the sample's histogram, within `hist`
   using K = RowKey<DT>;
   constexpr int NW = BS / kWave;
   constexpr uint32_t RB = row_bins_per_thread<DT, BS>();  // log bins owned per thread

@@ -5,6 +5,8 @@
 // workgroups' lists, so stage 2 selects from that union only.
 #pragma once
 
+#include <type_traits>
+
 #include "device_common.h"
 #include "launch.h"
 
@@ -13,7 +15,10 @@ namespace profk {
 // Vector y of a batch: a workspace pointer (null stays null), the values.
 template <class T>
 __device__ __forceinline__ void at_vector(T*& p, uint64_t bytes) {
-  if (p) p = reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p) + bytes * blockIdx.y);
+  // (byte arithmetic on the pointer: through an integer the compiler would
+  // lose its address space and load with flat instructions)
+  using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+  if (p) p = reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + bytes * blockIdx.y);
 }
 
 // Clears the per-call counters; fhist (kLogBins words, or null) is the
