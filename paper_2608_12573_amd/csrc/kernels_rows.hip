@@ -27,7 +27,16 @@ __host__ __device__ constexpr bool row_fast_tau(uint32_t S, int bs) { return S <
 
 // Log-scale buckets of a row workgroup: the buckets of a row key's distance,
 // padded so that every thread owns the same number.
-template <int DT, int BS> constexpr uint32_t row_bins_per_thread() { return (row_log_bins<DT>() + BS - 1) / BS; }
+// A block of one wave takes eight log bins as one bucket: a short row's few
+// hundred survivors leave them small, and clearing and scanning 3328 counters
+// would cost more than the survivors do.
+template <int BS> constexpr uint32_t row_bin_shift() { return BS == kRowShortBS ? 3u : 0u; }
+template <int DT, int BS> constexpr uint32_t row_bins_per_thread() {
+  return ((row_log_bins<DT>() >> row_bin_shift<BS>()) + BS - 1) / BS;
+}
+// Radix digit of the refinement and fallback in a block of one wave: eight
+// bits, whose histogram fits beside its other arrays.
+template <int DT, int BS> constexpr int row_block_digit() { return BS == kRowShortBS ? 8 : row_digit<DT>(); }
 
 struct RowArgs {
   const void* values;
@@ -45,11 +54,12 @@ struct RowArgs {
 // drawn, so that the sample's latency and the stream's overlap; it takes
 // registers that a workgroup among many on its CU has no use for.
 template <int DT, bool LEX, int BS, bool PRE>
-__global__ __launch_bounds__(BS) void k_rows(RowArgs a) {
+__global__ __launch_bounds__(BS, BS == kRowShortBS ? 4 : 1) void k_rows(RowArgs a) {
+  constexpr int U = BS == kRowShortBS ? kRowShortU : kRowU;
   constexpr int ES = Elem<DT>::ES, EPV = Elem<DT>::EPV, KB = Elem<DT>::KEYBITS;
   constexpr int kSelDigitRow = KB == 16 ? 8 : 11;  // sample select: 2 or 3 passes
-  constexpr int kDigit = row_digit<DT>();
-  constexpr int kTauDigit = 10;                        // the sample's histogram, within `hist`
+  constexpr int kDigit = row_block_digit<DT, BS>();
+  constexpr int kTauDigit = BS == kRowShortBS ? kRowTauDigit : 10;  // the sample's histogram, within `hist`
   using K = RowKey<DT>;
   constexpr int NW = BS / kWave;
   constexpr uint32_t RB = row_bins_per_thread<DT, BS>();  // log bins owned per thread
@@ -80,15 +90,16 @@ __global__ __launch_bounds__(BS) void k_rows(RowArgs a) {
   const u32x4* vec = reinterpret_cast<const u32x4*>(row + static_cast<size_t>(head) * ES);
 
   uint32_t status = PROFK_STATUS_DIRECT, count = 0, tau = 0, gmax = 0;
+  auto bucket = [&](uint32_t key) { return log_bin(key - tau) >> row_bin_shift<BS>(); };
   if (!a.direct) {
-    u32x4 v[kRowU];
-    // one step of the stream, kRowU vectors per thread (nvec > 0): past the
+    u32x4 v[U];
+    // one step of the stream, U vectors per thread (nvec > 0): past the
     // end the last vector is read again, and the exact test skips it.
     // (branch-free: with a branch per vector and v outside the loop the
     // compiler waits for each load before it issues the next)
     auto load_step = [&](uint32_t vb) {
 #pragma unroll
-      for (int u = 0; u < kRowU; ++u) v[u] = __builtin_nontemporal_load(vec + min(vb + u * BS + tid, nvec - 1));
+      for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(vec + min(vb + u * BS + tid, nvec - 1));
     };
     if (PRE && nvec) load_step(0);
     // 1. sample: the Philox words first, then all gathers in flight at once
@@ -189,9 +200,12 @@ __global__ __launch_bounds__(BS) void k_rows(RowArgs a) {
         bidx[slot] = idx;
       }
     };
-    for (uint32_t vb = 0; vb < nvec; vb += BS * kRowU) {
-      if (!PRE || vb) load_step(vb);
-      const TileSparse<DT, kRowU, BS, LEX> tx(v, th, vb, nvec, tid, head);
+    for (uint32_t vb = 0; vb < nvec; vb += BS * U) {
+      constexpr bool kOne = BS == kRowShortBS;  // the row is one step
+      if constexpr (!kOne) {
+        if (!PRE || vb) load_step(vb);
+      }
+      const TileSparse<DT, U, BS, LEX> tx(v, th, vb, nvec, tid, head);
       if (__ballot(tx.any()) == 0) continue;
       uint32_t slot = reserve(tx.count());
       tx.emit(v, [&](uint32_t key, uint32_t idx) { store(slot++, key, idx); });
@@ -223,7 +237,7 @@ __global__ __launch_bounds__(BS) void k_rows(RowArgs a) {
     if (status == PROFK_STATUS_FILTERED) {
       // bucket histogram of the buffer (after the pass, so that the
       // streaming loop does no per-survivor histogram atomics)
-      for (uint32_t i = tid; i < count; i += BS) atomicAdd(&hist[log_bin(bkey[i] - tau)], 1u);
+      for (uint32_t i = tid; i < count; i += BS) atomicAdd(&hist[bucket(bkey[i])], 1u);
       __syncthreads();
     }
   }
@@ -266,13 +280,13 @@ __global__ __launch_bounds__(BS) void k_rows(RowArgs a) {
       // and hist[b + 1] its start
       for (uint32_t i = tid; i < count; i += BS) {
         const uint32_t key = bkey[i];
-        const uint32_t bin = log_bin(key - tau);
+        const uint32_t bin = bucket(key);
         if (bin >= bstar) comp[atomicAdd(&hist[bin], 1u)] = composite(key, bidx[i]);
       }
       __syncthreads();
       for (uint32_t p = tid; p < n_sel; p += BS) {
         const uint64_t c = comp[p];
-        const uint32_t bin = log_bin(comp_key(c) - tau);
+        const uint32_t bin = bucket(comp_key(c));
         const uint32_t s0 = bin + 1 < NB ? hist[bin + 1] : 0u, s1 = hist[bin];
         uint32_t rank = 0;
         for (uint32_t q = s0; q < s1; ++q) rank += comp[q] > c ? 1u : 0u;
@@ -323,8 +337,10 @@ RowLayout row_layout(const profk_plan_t& p, int dtype, int bs) {
   const uint32_t key_bytes = M * (f32 ? 4u : 2u);
   uint32_t a_bytes = align16(samp_bytes > key_bytes ? samp_bytes : key_bytes);
   if (a_bytes + b_bytes < exch) a_bytes = exch - b_bytes;
-  const uint32_t nb = (f32 ? row_log_bins<0>() : row_log_bins<1>()) + ubs - 1;
-  const uint32_t radix = 1u << (f32 ? row_digit<0>() : row_digit<1>());
+  const bool wave = bs == kRowShortBS;
+  const uint32_t nb = ((f32 ? row_log_bins<0>() : row_log_bins<1>()) >> (wave ? row_bin_shift<kRowShortBS>() : 0u)) + ubs - 1;
+  // the radix digit's histogram; in a block of one wave the sample's is larger
+  const uint32_t radix = 1u << (wave ? kRowTauDigit : f32 ? row_digit<0>() : row_digit<1>());
   uint32_t hist_words = radix;
   if (hist_words < nb / ubs * ubs) hist_words = nb / ubs * ubs;
   L.off_a = 0;
@@ -356,6 +372,11 @@ bool rows_fit_block(const profk_plan_t& p, int dtype) {
 //   4096 of 256 KB (bf16): 215 / 203 / 313;  1024 of 400 KB: 90 / 83 / 105;
 //   1024 of 128 KB: 36.8 / 37.0 / 62;  4096 of 64 KB: 68 / 80 / 193;
 //   8192 of 16 KB: 74 / 118 / 304;  16 of 16 KB: 16 / - / 16.
+// A large batch of rows that one wave holds in registers takes a wave per row:
+// there a block's barriers and the passes of four waves over its counters cost
+// more than the row (256 / 64 threads: 8192 rows of 16 KB 72 / 61, of 4 KB
+// 70 / 34; 512 of 16 KB 17 / 19).  The lexicographic rule does not fit its
+// registers.
 // The vector path (sample, filter, refinement: three launches of which each
 // takes R rows) shares every row out over the chip, which pays where a row is
 // long and the rows are few.  Measured (us, 1024 threads / vector path, k = 32
@@ -377,6 +398,9 @@ int rows_block_threads(const profk_plan_t& p, int dtype, int64_t B, int64_t R, i
     if (block_us > vector_us) return 0;
   }
   if (!small) return B > num_cus && fits(kRowMidBS) ? kRowMidBS : kRowWideBS;
+  if (p.N * (dtype == PROFK_F32 ? 4 : 2) <= kRowShortBytes && B >= 4 * num_cus && p.mode == PROFK_MODE_FILTER &&
+      !p.lexicographic && p.k <= kRowShortBS * 4 && p.S <= kRowShortBS * 8 && p.M <= kRowShortM)
+    return kRowShortBS;
   if (kb >= 32 && B <= num_cus && wide) return kRowWideBS;
   if (kb >= 128 && fits(kRowMidBS)) return kRowMidBS;
   return kRowBS;
@@ -389,13 +413,19 @@ static hipError_t launch_rows_t(const RowCall& c) {
              static_cast<uint32_t>(p.t), static_cast<uint32_t>(p.M), p.mode == PROFK_MODE_DIRECT ? 1 : 0,
              c.seed, c.out_vals, c.out_idx, c.info, row_layout(p, c.dtype, BS)};
   const uint32_t lds = ra.L.bytes;
-  if (p.lexicographic) hipLaunchKernelGGL((k_rows<DT, true, BS, PRE>), dim3(c.B), dim3(BS), lds, c.stream, ra);
-  else hipLaunchKernelGGL((k_rows<DT, false, BS, PRE>), dim3(c.B), dim3(BS), lds, c.stream, ra);
+  if constexpr (BS != kRowShortBS) {
+    if (p.lexicographic) {
+      hipLaunchKernelGGL((k_rows<DT, true, BS, PRE>), dim3(c.B), dim3(BS), lds, c.stream, ra);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_rows<DT, false, BS, PRE>), dim3(c.B), dim3(BS), lds, c.stream, ra);
   return hipGetLastError();
 }
 
 template <int DT>
 static hipError_t launch_rows_dt(const RowCall& c) {
+  if (c.threads == kRowShortBS) return launch_rows_t<DT, kRowShortBS, true>(c);
   if (c.threads == kRowWideBS) return launch_rows_t<DT, kRowWideBS, true>(c);
   if (c.threads == kRowMidBS) return launch_rows_t<DT, kRowMidBS, true>(c);
   return launch_rows_t<DT, kRowBS, false>(c);

@@ -195,6 +195,11 @@ hipError_t launch_big(const BigCall& c);
 
 // Per-row kernel: one workgroup per row, everything in LDS.
 constexpr int kRowBS = 256;                   // threads of a row block: short rows,
+constexpr int kRowShortBS = 64;               // rows one wave holds in registers (a large batch of them),
+constexpr int kRowShortU = 16;                // ... 16-byte vectors per lane,
+constexpr int64_t kRowShortBytes = kRowShortBS * kRowShortU * 16;
+constexpr int64_t kRowShortM = 1024;          // ... and their largest buffer
+constexpr int kRowTauDigit = 9;               // ... digit of its sample's histogram
 constexpr int kRowMidBS = 512;                // long rows,
 constexpr int kRowWideBS = 1024;              // few rows or a large k (rows_block_threads)
 constexpr int kRowU = 8;                      // 16-byte loads in flight per lane

@@ -78,3 +78,24 @@ def test_row_block_direct():
     p = pk.plan_rows(9001, 1500)
     assert p.mode == pk.MODE_DIRECT
     check_rows(_bits("f32", 7, 9001, seed=5), "f32", 1500, p, oracle_plan_of(p, rows=True), 0)
+
+
+@pytest.mark.parametrize("dtype,D,k,offset,extra", [
+    ("f32", 4096, 64, 0, 0), ("f32", 4095, 90, 1, 2), ("f32", 1501, 150, 0, 0), ("f32", 700, 1, 3, 1), ("f32", 2051, 30, 0, 5),
+    ("bf16", 8192, 64, 0, 0), ("bf16", 8191, 60, 5, 3), ("bf16", 1500, 3, 1, 0),
+])
+def test_row_block_one_wave(dtype, D, k, offset, extra):
+    """A wave per row (large batches of rows up to 16 KiB), full and ragged
+    widths, unaligned rows, with rows of ties and of few distinct values,
+    whose buckets are large or which overflow the buffer and fall back."""
+    B = 1030
+    b = _bits(dtype, B, D, seed=D + k)
+    one, two = (okeys.f32_bits(np.array([1.5], np.float32))[0], okeys.f32_bits(np.array([2.0], np.float32))[0]) \
+        if dtype == "f32" else workloads.f32_to_bf16_bits(np.array([1.5, 2.0], np.float32))
+    b[3] = one
+    b[5] = np.where(np.arange(D) % 3 == 0, two, one)
+    b[7, : D - D // 8] = 0
+    p = pk.plan_rows(D, k)
+    assert p.mode == pk.MODE_FILTER and p.S <= 512 and p.M <= 1024
+    st = check_rows(b, dtype, k, p, oracle_plan_of(p, rows=True), 1, offset=offset, stride=D + extra)
+    assert st.count(oprofk.STATUS_FILTERED) >= B - 3 and oprofk.STATUS_OVERFLOW in st
