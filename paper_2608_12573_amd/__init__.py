@@ -171,9 +171,17 @@ def workspace_size(p, dtype, batch=1):
 
 # ----------------------------------------------------------- torch side ---
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    """torch, imported on first use (the import statement costs about a
+    microsecond of each call's checks otherwise)."""
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _dtype_code(t):
@@ -186,12 +194,14 @@ def _dtype_code(t):
 
 
 def _stream():
+    """The current stream's handle (torch.cuda.current_stream() builds a Stream
+    object around it)."""
     torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def rows_workspace_size(p, dtype, B):

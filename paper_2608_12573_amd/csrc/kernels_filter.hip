@@ -125,7 +125,17 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
 
   // ---- threshold (stage 2) when the sample union is small
   uint32_t tau;
-  if (a.union_n) {
+  if (a.union_n > 0 && a.union_n <= kFiltTauList) {
+    // so few keys are ranked by counting at once
+    static_assert(kFiltTauList <= kFiltBS && kListWords <= kFiltBS && kFiltTauList <= kListRankMax, "a key per thread");
+    uint32_t* const list = s_pool + (1u << kTauDigit);
+    list[tid] = tid < a.union_n ? uk[0] : 0u;
+    __syncthreads();
+    list_kth<kFiltBS>(list, a.union_n, a.t, s_sc.found);
+    __syncthreads();
+    tau = s_sc.found[0];
+    if (b == 0 && tid == 0) a.st->tau_key = tau;
+  } else if (a.union_n) {
     tau = block_kth_regs<kFiltBS, E, kTauDigit>(uk, valid, min(a.union_n, static_cast<uint32_t>(kFiltBS)), a.t, s_pool,
                                                   s_pool + (1u << kTauDigit), s_red, s_sc)
               .x;

@@ -16,6 +16,7 @@
 //                 block computes the exact top-k of its chunk of the input,
 //                 the last of each group of 16 chunks to finish merges the
 //                 group's, and the last group to finish merges the groups'.
+#include <atomic>
 #include <climits>
 #include <cmath>
 
@@ -1327,11 +1328,18 @@ hipError_t launch_debug_filter(const FlatCall& c, uint32_t* buf_key, uint32_t* b
 }
 
 int device_cu_count() {
+  // a property of the device, asked once per device (every thread writes the
+  // same value)
+  constexpr int kDevices = 64;
+  static std::atomic<int> known[kDevices];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 256;
-  int cus = 0;
+  const bool slot = dev >= 0 && dev < kDevices;
+  int cus = slot ? known[dev].load(std::memory_order_relaxed) : 0;
+  if (cus > 0) return cus;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     return 256;
+  if (slot) known[dev].store(cus, std::memory_order_relaxed);
   return cus;
 }
 

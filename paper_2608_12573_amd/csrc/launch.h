@@ -65,6 +65,9 @@ constexpr uint64_t kFiltSparseInvDensity = 4096;        // "rare": t/(S+1) below
 // of every block and overlaps its first loads, where k_select_tau is a
 // launch of 9 us (BatchTopK, 2^28 values, t = 188: 223 -> 214 us).
 constexpr uint32_t kFiltTauMax = 2048;
+// Largest union it ranks by counting alone (N = 2548523, k = 1, 78 keys:
+// 18.8 us by groups, 17.9 by counting).  Capped lists are longer.
+constexpr uint32_t kFiltTauList = 128;
 constexpr uint32_t kStage = 1024;             // survivors a filter block stages in LDS
 constexpr int kSegs = 8;                      // candidate segments (one counter each)
 constexpr int kSegStride = 64;                // words between segment counters
