@@ -655,6 +655,36 @@ __device__ __forceinline__ uint2 block_kth_regs(const uint32_t (&kv)[E], uint32_
   return uint2{base, above};
 }
 
+// The kk-th largest (1-based, with multiplicity) of the keys one wave holds in
+// registers (E per lane, `valid` bits mark which), in every lane: bisection
+// over the bits of their distances from the smallest, the keys at or above a
+// candidate counted by ballots.  Requires 1 <= kk <= #keys.  About 60 cycles
+// per bit and no LDS, so a block's other waves are free.
+template <int E>
+__device__ __forceinline__ uint32_t wave_kth(const uint32_t (&kv)[E], uint32_t valid, uint32_t kk) {
+  uint32_t mx = 0, nmn = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const bool in = (valid >> e) & 1u;
+    mx = max(mx, in ? kv[e] : 0u);
+    nmn = max(nmn, in ? ~kv[e] : 0u);
+  }
+  mx = wave_max_u32(mx);
+  const uint32_t mn = ~wave_max_u32(nmn);
+  uint32_t d[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) d[e] = ((valid >> e) & 1u) ? kv[e] - mn : 0u;  // (0 is never counted)
+  uint32_t res = 0;
+  for (int bit = mx == mn ? -1 : 31 - __clz(mx - mn); bit >= 0; --bit) {
+    const uint32_t cand = res | (1u << bit);
+    uint32_t n = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) n += static_cast<uint32_t>(__popcll(__ballot(d[e] >= cand)));
+    if (n >= kk) res = cand;
+  }
+  return mn + res;
+}
+
 // Number of leading bits shared by every value in [lo, hi] (lo <= hi),
 // counted within the low `nbits` bits.
 __device__ __forceinline__ int shared_prefix_bits(uint32_t lo, uint32_t hi, int nbits) {

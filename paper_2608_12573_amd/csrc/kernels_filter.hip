@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
   static_assert((1u << kTauDigit) + kListWords <= kLogBins, "select of tau");
   __shared__ __align__(16) uint32_t s_red[kKthRed];
   __shared__ SelectScratch s_sc;
-  __shared__ uint32_t s_cnt, s_base;
+  __shared__ uint32_t s_cnt, s_base, s_tau;
   __shared__ uint32_t s_wmax[kFiltBS / kWave];
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), b = blockIdx.x;
   const uint32_t seg = b & (kSegs - 1);
@@ -92,12 +92,14 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
   const uint32_t vend = a.nvec;
   const uint32_t vstride = gridDim.x * kTile;
   constexpr int E = kFiltTauMax / kFiltBS;
+  const bool one_wave = a.union_n <= kFiltTauWave * kWave;
   uint32_t uk[E];
   uint32_t valid = 0, cutv = 0;
   if (a.union_n) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const uint32_t i = tid + kFiltBS * e;
+      // one wave: lane + 64 e (every wave holds them); else tid + 256 e
+      const uint32_t i = one_wave ? lane + kWave * e : tid + kFiltBS * e;
       uk[e] = a.union_keys[min(i, a.union_n - 1)];
       if (i < a.union_n) valid |= 1u << e;
     }
@@ -125,16 +127,19 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
 
   // ---- threshold (stage 2) when the sample union is small
   uint32_t tau;
-  if (a.union_n > 0 && a.union_n <= kFiltTauList) {
-    // so few keys are ranked by counting at once
-    static_assert(kFiltTauList <= kFiltBS && kListWords <= kFiltBS && kFiltTauList <= kListRankMax, "a key per thread");
-    uint32_t* const list = s_pool + (1u << kTauDigit);
-    list[tid] = tid < a.union_n ? uk[0] : 0u;
+  if (a.union_n > 0 && one_wave && !a.all_keys) {
+    if (tid < kWave) {
+      uint32_t few[kFiltTauWave];
+#pragma unroll
+      for (uint32_t e = 0; e < kFiltTauWave; ++e) few[e] = uk[e];
+      const uint32_t x = wave_kth<kFiltTauWave>(few, valid, a.t);
+      if (lane == 0) {
+        s_tau = x;
+        if (b == 0) a.st->tau_key = x;
+      }
+    }
     __syncthreads();
-    list_kth<kFiltBS>(list, a.union_n, a.t, s_sc.found);
-    __syncthreads();
-    tau = s_sc.found[0];
-    if (b == 0 && tid == 0) a.st->tau_key = tau;
+    tau = s_tau;
   } else if (a.union_n) {
     tau = block_kth_regs<kFiltBS, E, kTauDigit>(uk, valid, min(a.union_n, static_cast<uint32_t>(kFiltBS)), a.t, s_pool,
                                                   s_pool + (1u << kTauDigit), s_red, s_sc)

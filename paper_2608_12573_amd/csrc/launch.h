@@ -65,9 +65,10 @@ constexpr uint64_t kFiltSparseInvDensity = 4096;        // "rare": t/(S+1) below
 // of every block and overlaps its first loads, where k_select_tau is a
 // launch of 9 us (BatchTopK, 2^28 values, t = 188: 223 -> 214 us).
 constexpr uint32_t kFiltTauMax = 2048;
-// Largest union it ranks by counting alone (N = 2548523, k = 1, 78 keys:
-// 18.8 us by groups, 17.9 by counting).  Capped lists are longer.
-constexpr uint32_t kFiltTauList = 128;
+// Union keys per lane when one wave selects tau and the others wait: with four
+// workgroups on a CU the select of all four waves costs 1.3 us more (17.9 M
+// values, 160 keys, t = 5: filter 17.0 against 15.4 us).
+constexpr uint32_t kFiltTauWave = 4;
 constexpr uint32_t kStage = 1024;             // survivors a filter block stages in LDS
 constexpr int kSegs = 8;                      // candidate segments (one counter each)
 constexpr int kSegStride = 64;                // words between segment counters
