@@ -45,8 +45,8 @@ FLUSH_BYTES = 512 << 20
 # for this exact code and are dropped once any of these changes).
 KERNELS = {
     "filter": {"match": "k_filter<0, false,", "what": "profk::k_filter<0, false, U> (fp32 filter-and-compact)",
-               "sources": ("kernels_filter.hip", "filter_tile.h", "device_common.h", "launch.h")},
-    "rows": {"match": "k_rows<1, false>", "what": "profk::k_rows<1, false> (bf16 per-row Prof-K, one workgroup per row)",
+               "sources": ("kernels_filter.hip", "filter_tile.h", "sample_union.h", "device_common.h", "launch.h")},
+    "rows": {"match": "k_rows<1, false,", "what": "profk::k_rows<1, false, 512, true> (bf16 per-row Prof-K, one workgroup per row)",
              "sources": ("kernels_rows.hip", "filter_tile.h", "topk_block.h", "device_common.h", "launch.h")},
     "sae": {"match": "k_sae_filter", "what": "profk::k_sae_filter (bf16 MFMA encoder GEMM + filter epilogue)",
             "sources": ("kernels_sae.hip", "sample_union.h", "device_common.h", "launch.h")},

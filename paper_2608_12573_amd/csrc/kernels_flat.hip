@@ -7,7 +7,8 @@
 //                 t > 32): Philox draws, gathers, and each block's local
 //                 top-t sample keys (the t-th largest of the whole sample is
 //                 among the union of the blocks' top-t).
-//   k_select_tau  only when that union is large: one block picks tau.
+//   k_select_tau  only when that union is large: one block picks tau
+//                 (lexicographic plans always take it).
 //   k_tau_index   lexicographic plans only: the sample blocks list the draws
 //                 that carry tau, and the last one picks the threshold pair.
 //   k_filter      the filter-and-compact pass (kernels_filter.hip).
@@ -16,6 +17,8 @@
 //                 block computes the exact top-k of its chunk of the input,
 //                 the last of each group of 16 chunks to finish merges the
 //                 group's, and the last group to finish merges the groups'.
+// Small vectors without sampling take k_small instead (kernels_small.hip).
+// The kernels of a batch (template argument BATCH) take vector blockIdx.y.
 #include <atomic>
 #include <climits>
 #include <cmath>

@@ -1,9 +1,10 @@
 // Per-row Prof-K (Sec. 3: for batched inputs the procedure runs on each
-// batch element).  One workgroup owns one row and runs all four stages in
-// LDS:
+// batch element).  One workgroup of 64 to 1024 threads owns one row and runs
+// all four stages in LDS:
 //   1. draw S indices of the row (Philox counter word 1 = row);
-//   2. tau = t-th largest sampled key (radix select in LDS); lexicographic
-//      plans also find the index of the threshold pair;
+//   2. tau = t-th largest sampled key (from registers when they hold the
+//      sample, else a radix select in LDS); lexicographic plans also find the
+//      index of the threshold pair;
 //   3. stream the row once with 16-byte loads, appending survivors to an
 //      LDS buffer of capacity M and counting all of them; a buffer that
 //      holds them all is then histogrammed by log_bin(key - tau);

@@ -792,11 +792,11 @@ __device__ __forceinline__ void dec_sum_chunk(const DecArgs& a, uint32_t r, uint
 // What bounds it: the rows of W_dec it reads (K of them, 134 MB at B = 4096,
 // d_model = 512, K = 131072, from the caches, at about 40 GB/s per CU).  A
 // workgroup holds kDecCap entries (bitmaps of latents, whose prefix sums give
-// each entry its place);
-// rows that have more together are taken in smaller runs, and a single row
-// with more as a value per latent.  One workgroup per row, with a flag and a
-// value per latent in LDS (one workgroup of 256 threads per CU), took 146 us
-// at that shape and grouping the list 24 us before it; this takes 34 in all.
+// each entry its place); rows that have more together are taken in smaller
+// runs, and a single row with more as a value per latent.  One workgroup per
+// row, with a flag and a value per latent in LDS (one workgroup of 256
+// threads per CU), took 146 us at that shape and grouping the list 24 us
+// before it; this takes 33 in all.
 template <bool VEC>
 __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
   constexpr int NW = kDecBS / kWave;

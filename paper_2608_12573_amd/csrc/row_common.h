@@ -1,6 +1,4 @@
-// Definitions shared by the two per-row kernels (one workgroup per row with
-// the row streamed through LDS, and one workgroup per compute unit holding
-// whole rows in registers).
+// Key and bucket types of the per-row kernel.
 #pragma once
 
 #include <type_traits>
