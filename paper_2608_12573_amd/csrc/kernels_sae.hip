@@ -822,19 +822,21 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
     const uint64_t span = static_cast<uint64_t>(nrows) * a.d_dict;  // (lo + span <= B * d_dict)
     const uint32_t lanes = a.groups > 1 ? kDecLanes : kDecBS;
     for (uint32_t ch = tid / lanes; ch < a.chunks; ch += kDecBS / lanes) {
-      uint32_t b = ch * kDecChunk, e1 = min(b + kDecChunk, a.K);
+      // entries [b, b + len); offsets are compared with len, since positions
+      // past b + len may pass 2^32
+      uint32_t b = ch * kDecChunk, len = min(kDecChunk, a.K - b);
       if (a.groups > 1) {
         const uint32_t* const start = a.start + static_cast<size_t>(ch) * (a.groups + 1) + group;
         b = start[0];
-        e1 = start[1];
+        len = start[1] - b;
       }
       constexpr uint32_t U = kDecPer;  // a whole chunk per step when ungrouped
-      for (b += tid % lanes; b < e1; b += lanes * U) {
+      for (uint32_t q = tid % lanes; q < len; q += lanes * U) {
         uint32_t pe[U];
         int64_t fi[U];
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
-          pe[u] = min(b + u * lanes, e1 - 1);
+          pe[u] = b + min(q + u * lanes, len - 1);
           if (a.groups > 1) pe[u] = a.grouped[pe[u]];
         }
 #pragma unroll
@@ -843,7 +845,7 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
         for (uint32_t u = 0; u < U; ++u) {
           // (entries of rows below, and padding, wrap past the span)
           const uint64_t o = static_cast<uint64_t>(fi[u] - lo);
-          if (o < span && b + u * lanes < e1) f(pe[u], static_cast<uint32_t>(o));
+          if (o < span && q + u * lanes < len) f(pe[u], static_cast<uint32_t>(o));
         }
       }
     }
