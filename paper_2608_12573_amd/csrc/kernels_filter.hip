@@ -92,7 +92,10 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
   const uint32_t vend = a.nvec;
   const uint32_t vstride = gridDim.x * kTile;
   constexpr int E = kFiltTauMax / kFiltBS;
-  const bool one_wave = a.union_n <= kFiltTauWave * kWave;
+  // One wave selects tau from a small union, of which every wave then holds a
+  // copy.  Capped lists (all_keys) are selected by the whole block, each key
+  // held once, since every thread takes part in the check of the cut keys.
+  const bool one_wave = !a.all_keys && a.union_n <= kFiltTauWave * kWave;
   uint32_t uk[E];
   uint32_t valid = 0, cutv = 0;
   if (a.union_n) {
@@ -127,7 +130,7 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
 
   // ---- threshold (stage 2) when the sample union is small
   uint32_t tau;
-  if (a.union_n > 0 && one_wave && !a.all_keys) {
+  if (a.union_n > 0 && one_wave) {
     if (tid < kWave) {
       uint32_t few[kFiltTauWave];
 #pragma unroll

@@ -71,3 +71,43 @@ def test_row_tau(dtype, D, k, S):
     p = pk.plan_rows(D, k, **kw)
     q = oracle_plan_of(p, opts=dataclasses.replace(oplan.ROW_OPTS, S_min=S, S_max=S, force_mode=pk.FORCE_FILTER))
     check_rows(bits.reshape(3, D), dtype, k, p, q, 2)
+
+
+def _capped_union(p):
+    """Keys in the union of the plan's capped sample lists (blocks of 1024
+    draws, each list at most 16 or 32 long, the draws of a block in the top t
+    plus eight standard deviations), 0 when its lists are not capped."""
+    if p.t <= 32 or p.S < 2 * 1024 or p.lexicographic:
+        return 0
+    mu = 1024 * p.t / p.S
+    need = mu + 8 * mu**0.5 + 2
+    cap = 16 if need <= 16 else 32 if need <= 32 else 0
+    whole, last = divmod(p.S - 1, 1024)
+    return whole * cap + min(cap, last + 1) if cap else 0
+
+
+@pytest.mark.parametrize("dtype,B,D,k,kw", [
+    ("f32", 1, 393216, 1000, {}), ("f32", 16, 370727, 1024, {}), ("f32", 3, 524288, 1500, {}),
+    ("bf16", 4, 370727, 1024, {}), ("f32", 4, 393216, 1000, dict(recall=0.9)), ("f32", 2, 524288, 1100, {}),
+])
+def test_row_tau_small_capped_union(dtype, B, D, k, kw):
+    """Capped lists whose union has at most 256 keys, which one wave could
+    hold: default row plans on the vector path, all filtered."""
+    p = pk.plan_rows(D, k, **kw)
+    code = pk.F32 if dtype == "f32" else pk.BF16
+    assert p.t > 32 and 0 < _capped_union(p) <= 256
+    assert pk.rows_workspace_size(p, code, B) == B * pk.workspace_size(p, code, 1)
+    x = _values("normal", B * D, B + k).reshape(B, D)
+    bits = okeys.f32_bits(x) if dtype == "f32" else workloads.f32_to_bf16_bits(x).reshape(B, D)
+    st = check_rows(bits, dtype, k, p, oracle_plan_of(p, rows=True), 5)
+    assert st == [oprofk.STATUS_FILTERED] * B
+
+
+@pytest.mark.parametrize("S,k,N,union", [(5000, 1000, 400000, 160), (5121, 1100, 400000, 161), (7169, 1250, 400000, 225),
+                                         (8192, 1100, 300000, 256), (8193, 1100, 300000, 257),
+                                         (16384, 740, 1000000, 256), (16385, 740, 1000000, 257)])
+def test_vector_tau_small_capped_union(S, k, N, union):
+    """Both sides of 256 keys, lists of 16 and 32 and a last list of one."""
+    p = pk.plan(N, k, S_min=S, S_max=S, force_mode=pk.FORCE_FILTER)
+    assert _capped_union(p) == union, (p.t, _capped_union(p))
+    _check(_values("normal", N, S), k, 4, S_min=S, S_max=S, force_mode=pk.FORCE_FILTER)
