@@ -678,10 +678,10 @@ constexpr int kDecBS = 1024;
 constexpr uint32_t kDecRows = 16;        // rows of a workgroup: one wave each
 constexpr uint32_t kDecCap = 8192;       // entries of a workgroup's rows held at once
 constexpr uint32_t kDecWords = kDecMaxDict / 32;
-constexpr uint32_t kDecPer = 4;          // list entries per thread of a chunk
-constexpr uint32_t kDecChunk = kDecPer * kDecBS;
+constexpr uint32_t kDecPer = 4;          // list entries per thread and step
+constexpr uint32_t kDecStep = kDecPer * kDecBS;
 constexpr uint32_t kDecMaxGroups = kDecBS;
-constexpr uint32_t kDecLanes = 16;       // lanes that read a group's entries of one chunk
+constexpr uint32_t kDecLanesLog2 = 4;    // fewest lanes that read a group's entries of one chunk
 constexpr uint32_t kDecUngrouped = 16384;  // longest list that every workgroup reads whole
 
 struct DecArgs {
@@ -694,33 +694,53 @@ struct DecArgs {
   uint32_t rows;       // rows of a workgroup, at most kDecRows
   uint32_t groups;     // row groups, at most kDecMaxGroups
   uint32_t group_rows; // rows of a group, a multiple of `rows`
+  uint32_t chunk;      // entries of a chunk of the list, a multiple of kDecStep
   uint32_t chunks;     // chunks of the list
+  uint32_t lanes_log2; // lanes that read a group's entries of one chunk
   uint32_t* start;     // [chunks][groups + 1] first entry of each group in a chunk's order
   uint32_t* grouped;   // [K] list positions, each chunk's by group
 };
 
-// Chunk blockIdx.x of the list (kDecChunk entries) by row group: the positions
+// Chunk blockIdx.x of the list (a.chunk entries) by row group: the positions
 // of its valid entries, group by group, into `grouped` at the chunk's place.
+// ONE: the chunk is one step, held in registers; otherwise its entries are
+// read twice, to count and to place them.
 // What bounds it is latency (a few dependent steps on one chunk per
 // workgroup).  Counting rows, a prefix sum and a scatter through atomics on
 // a counter per row took four launches and 24 us for 131072 entries.
+template <bool ONE>
 __global__ __launch_bounds__(kDecBS) void k_dec_group(DecArgs a) {
   __shared__ uint32_t hist[kDecMaxGroups];
   __shared__ uint32_t wsum[20];
-  const uint32_t tid = threadIdx.x, e0 = blockIdx.x * kDecChunk;
+  const uint32_t tid = threadIdx.x, e0 = blockIdx.x * a.chunk;
+  const uint32_t len = min(a.chunk, a.K - e0);
   const uint32_t span = a.group_rows * a.d_dict;  // latents of a group (groups > 1: less than B * d_dict)
   if (tid < a.groups) hist[tid] = 0;
+  // the entries from offset o on, one of each kDecBS per thread; their groups,
+  // and their places there from the counters (0xFFFFFFFF: no entry)
   int64_t f[kDecPer];
+  auto load = [&](uint32_t o) {
 #pragma unroll
-  for (uint32_t q = 0; q < kDecPer; ++q) f[q] = a.idx[min(e0 + q * kDecBS + tid, a.K - 1)];
-  __syncthreads();
+    for (uint32_t q = 0; q < kDecPer; ++q) f[q] = a.idx[e0 + min(o + q * kDecBS + tid, len - 1)];
+  };
   uint32_t g[kDecPer], at[kDecPer];
+  auto count = [&](uint32_t o) {
 #pragma unroll
-  for (uint32_t q = 0; q < kDecPer; ++q) {
-    const bool in = e0 + q * kDecBS + tid < a.K &&
-                    static_cast<uint64_t>(f[q]) < static_cast<uint64_t>(a.B) * a.d_dict;
-    g[q] = in ? static_cast<uint32_t>(f[q]) / span : 0xFFFFFFFFu;
-    at[q] = in ? atomicAdd(&hist[g[q]], 1u) : 0u;
+    for (uint32_t q = 0; q < kDecPer; ++q) {
+      const bool in = o + q * kDecBS + tid < len &&
+                      static_cast<uint64_t>(f[q]) < static_cast<uint64_t>(a.B) * a.d_dict;
+      g[q] = in ? static_cast<uint32_t>(f[q]) / span : 0xFFFFFFFFu;
+      at[q] = in ? atomicAdd(&hist[g[q]], 1u) : 0u;
+    }
+  };
+  load(0);
+  __syncthreads();
+  count(0);
+  if constexpr (!ONE) {
+    for (uint32_t o = kDecStep; o < len; o += kDecStep) {  // (o stays below 2^32: a.chunk is at most 2^31)
+      load(o);
+      count(o);
+    }
   }
   __syncthreads();
   uint32_t tot;
@@ -733,9 +753,19 @@ __global__ __launch_bounds__(kDecBS) void k_dec_group(DecArgs a) {
   }
   if (tid == 0) start[a.groups] = e0 + tot;
   __syncthreads();
+  if constexpr (ONE) {
 #pragma unroll
-  for (uint32_t q = 0; q < kDecPer; ++q)
-    if (g[q] != 0xFFFFFFFFu) a.grouped[e0 + hist[g[q]] + at[q]] = e0 + q * kDecBS + tid;
+    for (uint32_t q = 0; q < kDecPer; ++q)
+      if (g[q] != 0xFFFFFFFFu) a.grouped[e0 + hist[g[q]] + at[q]] = e0 + q * kDecBS + tid;
+  } else {
+    for (uint32_t o = 0; o < len; o += kDecStep) {
+      load(o);
+      count(o);
+#pragma unroll
+      for (uint32_t q = 0; q < kDecPer; ++q)
+        if (g[q] != 0xFFFFFFFFu) a.grouped[e0 + at[q]] = e0 + o + q * kDecBS + tid;
+    }
+  }
 }
 
 // Sums row r's entries into out[r, :]: entry(q) gives the q-th latent index
@@ -816,22 +846,22 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
   const uint32_t chunks = (a.d_model + kWave * (VEC ? 8 : 1) - 1) / (kWave * (VEC ? 8 : 1));
   const uint32_t group = r0 / a.group_rows;
   // visit(rb, nrows, f): f(e, o) for every entry e of rows [rb, rb + nrows),
-  // o its offset from the first latent of row rb; kDecLanes lanes to a chunk
+  // o its offset from the first latent of row rb; 2^lanes_log2 lanes to a chunk
   auto visit = [&](uint32_t rb, uint32_t nrows, auto f) {
     const int64_t lo = static_cast<int64_t>(rb) * a.d_dict;
     const uint64_t span = static_cast<uint64_t>(nrows) * a.d_dict;  // (lo + span <= B * d_dict)
-    const uint32_t lanes = a.groups > 1 ? kDecLanes : kDecBS;
-    for (uint32_t ch = tid / lanes; ch < a.chunks; ch += kDecBS / lanes) {
+    const uint32_t lanes = 1u << a.lanes_log2;
+    for (uint32_t ch = tid >> a.lanes_log2; ch < a.chunks; ch += kDecBS >> a.lanes_log2) {
       // entries [b, b + len); offsets are compared with len, since positions
       // past b + len may pass 2^32
-      uint32_t b = ch * kDecChunk, len = min(kDecChunk, a.K - b);
+      uint32_t b = ch * a.chunk, len = min(a.chunk, a.K - b);
       if (a.groups > 1) {
         const uint32_t* const start = a.start + static_cast<size_t>(ch) * (a.groups + 1) + group;
         b = start[0];
         len = start[1] - b;
       }
-      constexpr uint32_t U = kDecPer;  // a whole chunk per step when ungrouped
-      for (uint32_t q = tid % lanes; q < len; q += lanes * U) {
+      constexpr uint32_t U = kDecPer;  // (ungrouped: kDecStep entries per step)
+      for (uint32_t q = tid & (lanes - 1); q < len; q += lanes * U) {
         uint32_t pe[U];
         int64_t fi[U];
 #pragma unroll
@@ -856,7 +886,8 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
   float* const dense = reinterpret_cast<float*>(s_ent);
   uint32_t* const has = reinterpret_cast<uint32_t*>(s_pre);
   uint16_t* const order = reinterpret_cast<uint16_t*>(s_has);
-  // rows [rb, rb + c) at a time; c is halved when they have too many entries
+  // rows [rb, rb + c) at a time; when they have too many entries, c goes down
+  // to the rows that would fit if all had the same number
   uint32_t c = nr;
   for (uint32_t rb = 0; rb < nr;) {
     c = min(c, nr - rb);
@@ -875,7 +906,8 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
     __syncthreads();
     const uint32_t n = s_n;
     if (n > kDecCap && c > 1) {
-      c = (c + 1) / 2;
+      const uint32_t runs = (n - 1) / kDecCap + 1;  // (at least 2)
+      c = (c + runs - 1) / runs;
       continue;
     }
     if (n <= kDecCap) {
@@ -1075,26 +1107,65 @@ size_t sae_decode_workspace(uint32_t B, uint32_t K) {
   return (static_cast<size_t>(B) * 3 + 2 + K) * 4 + 256;
 }
 
+// How the list is split: chunks of it sorted by row group, with the groups'
+// starts in `table` words, chunks * (groups + 1) of them.  A long list has to
+// trade the two: few chunks leave few workgroups to sort it, few groups have
+// every workgroup read its neighbours' rows too, on each of its passes.  The
+// cost counts steps of kDecStep entries, two a step of a chunk that does not
+// fit one.  Chunks of one step always, and the groups that the table then
+// leaves, took 36.2 ms for 4096 rows of 16384 latents with 4096 entries each
+// (two groups, which every workgroup read a dozen times), this 15.5 ms.
+struct DecSplit {
+  uint32_t chunk, chunks, groups, group_rows, lanes_log2;
+};
+
+static DecSplit split_decode(uint32_t B, uint32_t K, uint32_t rows, uint64_t table, uint32_t cus) {
+  const uint32_t blocks = cdiv_s(B, rows), steps = cdiv_s(K, kDecStep);
+  DecSplit best{kDecStep, steps, 1, blocks * rows, 10};
+  // A short list is not grouped: every workgroup reads all of it (K = 8192:
+  // 15.2 us in all against 18.4 grouped; 32768: 27 against 26).
+  if (K <= kDecUngrouped) return best;
+  const double per_block = static_cast<double>(K) / B * rows;
+  const double passes = per_block <= kDecCap ? 1.0 : 1.0 + per_block / kDecCap;
+  const double rounds = cdiv_s(blocks, cus);
+  double least = rounds * passes * steps;
+  for (uint32_t m = cdiv_s(blocks, kDecMaxGroups); m < blocks; m += (m + 3) / 4) {  // m workgroups a group
+    const uint32_t groups = cdiv_s(blocks, m);
+    const uint64_t most = table / (groups + 1);
+    if (most == 0) continue;
+    const uint32_t per = cdiv_s(steps, most < steps ? static_cast<uint32_t>(most) : steps), chunks = cdiv_s(steps, per);
+    const double cost = static_cast<double>(cdiv_s(chunks, cus)) * (per > 1 ? 2 * per : 1) +
+                        rounds * passes * steps / groups;
+    if (cost < least) {
+      least = cost;
+      best = {per * kDecStep, chunks, groups, m * rows, 0};
+    }
+    if (per == 1) break;  // fewer groups only cost more
+  }
+  // Lanes for a group's entries of one chunk; all of the workgroup's threads
+  // have work where the chunks are few.
+  if (best.groups > 1) {
+    const uint32_t entries = best.chunk / best.groups;
+    best.lanes_log2 = kDecLanesLog2;
+    while (entries > 1u << best.lanes_log2 && static_cast<uint64_t>(best.chunks) << (best.lanes_log2 + 1) <= kDecBS)
+      ++best.lanes_log2;
+  }
+  return best;
+}
+
 hipError_t launch_sae_decode(const SaeDecodeCall& c) {
   (void)hipGetLastError();
   uint32_t* ws = static_cast<uint32_t*>(c.ws);
   const uint32_t cus = static_cast<uint32_t>(device_cu_count());
   const uint32_t rows = cdiv_s(c.B, cus) < kDecRows ? cdiv_s(c.B, cus) : kDecRows;
-  const uint32_t chunks = cdiv_s(c.K, kDecChunk);
-  // As many groups as the workspace has starts for, each whole workgroups.
   const uint32_t blocks = cdiv_s(c.B, rows);
   const uint64_t table = static_cast<uint64_t>(c.B) * 3 + 2;
-  // A short list is not grouped: every workgroup reads all of it (K = 8192:
-  // 15.2 us in all against 18.4 grouped; 32768: 27 against 26).
-  uint64_t most = c.K <= kDecUngrouped ? 1 : table / chunks;
-  most = most > 2 ? most - 1 : 1;
-  if (most > kDecMaxGroups) most = kDecMaxGroups;
-  const uint32_t group_rows = cdiv_s(blocks, most) * rows;
+  const DecSplit sp = split_decode(c.B, c.K, rows, table, cus);
   DecArgs a{c.vals, c.idx, c.K, c.B, c.d_model, c.d_dict, static_cast<const uint16_t*>(c.w), c.bias, c.out,
-            rows, cdiv_s(c.B, group_rows), group_rows, chunks, ws, ws + table};
-  // (a single group, also where rows have thousands of entries each, is the
-  // list as it stands)
-  if (a.groups > 1) hipLaunchKernelGGL(k_dec_group, dim3(chunks), dim3(kDecBS), 0, c.stream, a);
+            rows, sp.groups, sp.group_rows, sp.chunk, sp.chunks, sp.lanes_log2, ws, ws + table};
+  // (a single group is the list as it stands)
+  if (a.groups > 1 && a.chunk == kDecStep) hipLaunchKernelGGL(k_dec_group<true>, dim3(a.chunks), dim3(kDecBS), 0, c.stream, a);
+  else if (a.groups > 1) hipLaunchKernelGGL(k_dec_group<false>, dim3(a.chunks), dim3(kDecBS), 0, c.stream, a);
   const bool vec = c.d_model % 8 == 0 && reinterpret_cast<uintptr_t>(c.w) % 16 == 0;
   if (vec) hipLaunchKernelGGL(k_dec_rows<true>, dim3(blocks), dim3(kDecBS), 0, c.stream, a);
   else hipLaunchKernelGGL(k_dec_rows<false>, dim3(blocks), dim3(kDecBS), 0, c.stream, a);

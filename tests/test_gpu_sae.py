@@ -198,6 +198,10 @@ def test_sae_decode(B, d_model, d_dict, k_row):
     (4096, 33, 96, "spread"),         # columns not a multiple of eight
     (520, 64, 16384, "hot"),          # one row with more entries than are held at once
     (600, 64, 9000, "full"),          # three neighbouring rows, too many together
+    (256, 16, 2048, "half"),          # one row a workgroup, long chunks
+    (4096, 8, 512, "half"),           # sixteen rows a workgroup, more entries than it holds, long chunks
+    (4100, 24, 600, "half"),          # the same, the last workgroup and chunk in part
+    (24, 16, 16384, "half"),          # the largest count held at once, few workgroups
 ])
 def test_decode_layouts(B, d_model, d_dict, kind):
     """Rows per workgroup, column remainders, workgroups per group, and rows
@@ -212,6 +216,8 @@ def test_decode_layouts(B, d_model, d_dict, kind):
         idx = g.choice(B * d_dict, B * d_dict // 4, replace=False)
     elif kind == "hot":
         idx = np.concatenate([5 * d_dict + np.arange(d_dict), 400 * d_dict + np.arange(0, d_dict, 7)])
+    elif kind == "half":
+        idx = np.flatnonzero(g.random(B * d_dict) < 0.5)
     else:
         idx = np.concatenate([r * d_dict + np.arange(d_dict - 2) for r in {0, 1, B // 2, B - 1}])
     idx = g.permutation(idx).astype(np.int64)
@@ -231,3 +237,37 @@ def test_decode_layouts(B, d_model, d_dict, kind):
     np.add.at(mag, r, np.abs(v[:, None] * w[j]))
     terms = np.bincount(r, minlength=B)[:, None]
     assert np.all(np.abs(out - ref) <= (terms + 2) * 2.0**-24 * mag)
+
+
+def _decode_us(B, d_model, d_dict, k_row):
+    """Best of three decodes of k_row latents in each row, listed in random
+    order, by events."""
+    t = torch()
+    g = t.Generator(device="cuda").manual_seed(k_row)
+    j = (t.randint(0, d_dict, (B, 1), generator=g, device="cuda") + t.arange(k_row, device="cuda") * 4097) % d_dict
+    idx = (t.arange(B, device="cuda")[:, None] * d_dict + j).view(-1)
+    idx = idx[t.randperm(idx.numel(), generator=g, device="cuda")].contiguous()
+    vals = t.rand(idx.numel(), generator=g, device="cuda")
+    w = t.randn((d_dict, d_model), generator=g, device="cuda").to(t.bfloat16)
+    b = t.zeros(d_model, device="cuda")
+    note(f"decode time B={B} d_model={d_model} d_dict={d_dict} k_row={k_row}")
+    ev = [t.cuda.Event(enable_timing=True) for _ in range(2)]
+    best = float("inf")
+    for _ in range(4):
+        ev[0].record()
+        pk.sae_decode(vals, idx, w, b, B)
+        ev[1].record()
+        t.cuda.synchronize()
+        best = min(best, ev[0].elapsed_time(ev[1]) * 1e3)
+    return best
+
+
+def test_decode_time_follows_the_list():
+    """A dense list (a quarter of every row) costs in proportion to its
+    length: every workgroup reads its own rows' share of it, not the list.
+    Eight times the entries per row, of rows of eight columns, take about 50
+    times as long (rows that no longer fit a workgroup together are taken in
+    runs, each a pass over the share); with half the list read by every
+    workgroup it was 121 times."""
+    few, many = _decode_us(4096, 8, 16384, 512), _decode_us(4096, 8, 16384, 4096)
+    assert many < 80 * few, (few, many)
