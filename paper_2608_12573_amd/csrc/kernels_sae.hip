@@ -682,6 +682,13 @@ constexpr uint32_t kDecPer = 4;          // list entries per thread and step
 constexpr uint32_t kDecStep = kDecPer * kDecBS;
 constexpr uint32_t kDecMaxGroups = kDecBS;
 constexpr uint32_t kDecLanesLog2 = 4;    // fewest lanes that read a group's entries of one chunk
+// Fewest 64-column pieces of the rows in hand (two a wave) that are read eight
+// columns a lane.  With fewer pieces that left most waves without any: one
+// row of 512 columns was one wave's work (8 such rows with 4096 entries each
+// took 1284 us, 346 with a column a lane; 700 rows with 1024 entries 365 and 207).
+// At 32 pieces either is faster in places (1 row of 2048 columns with 512
+// entries: 93 us wide, 109 narrow; 1024 rows of 512 columns with 64: 35 and 27).
+constexpr uint32_t kDecWideMin = 32;
 constexpr uint32_t kDecUngrouped = 16384;  // longest list that every workgroup reads whole
 
 struct DecArgs {
@@ -827,6 +834,7 @@ __device__ __forceinline__ void dec_sum_chunk(const DecArgs& a, uint32_t r, uint
 // row, with a flag and a value per latent in LDS (one workgroup of 256
 // threads per CU), took 146 us at that shape and grouping the list 24 us
 // before it; this takes 33 in all.
+// VEC: W_dec can be read eight columns a lane (dec_sum_chunk).
 template <bool VEC>
 __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
   constexpr int NW = kDecBS / kWave;
@@ -843,7 +851,6 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   const uint32_t r0 = blockIdx.x * a.rows, nr = min(a.rows, a.B - r0);
   const uint32_t nw = (a.d_dict + 31) / 32;
-  const uint32_t chunks = (a.d_model + kWave * (VEC ? 8 : 1) - 1) / (kWave * (VEC ? 8 : 1));
   const uint32_t group = r0 / a.group_rows;
   // visit(rb, nrows, f): f(e, o) for every entry e of rows [rb, rb + nrows),
   // o its offset from the first latent of row rb; 2^lanes_log2 lanes to a chunk
@@ -878,6 +885,17 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
           if (o < span && q + u * lanes < len) f(pe[u], static_cast<uint32_t>(o));
         }
       }
+    }
+  };
+  // sum_rows(nrows, f): f(wide, row, chunk of columns) for every chunk of nrows
+  // rows, a wave each
+  auto sum_rows = [&](uint32_t nrows, auto f) {
+    const uint32_t narrow = (a.d_model + kWave - 1) / kWave;
+    if (VEC && nrows * narrow >= kDecWideMin) {
+      const uint32_t chunks = (narrow + 7) / 8;
+      for (uint32_t u = w; u < nrows * chunks; u += NW) f(std::true_type{}, u / chunks, u % chunks);
+    } else {
+      for (uint32_t u = w; u < nrows * narrow; u += NW) f(std::false_type{}, u / narrow, u % narrow);
     }
   };
   static_assert(sizeof(s_ent) >= kDecMaxDict * 4 && sizeof(uint16_t) * kDecMaxDict <= sizeof(s_has), "a dense row");
@@ -939,14 +957,14 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
         s_ord[at] = static_cast<uint16_t>(p);
       }
       __syncthreads();
-      for (uint32_t u = w; u < c * chunks; u += NW) {
-        const uint32_t rl = u / chunks, b = s_off[rl];
-        dec_sum_chunk<VEC>(a, r0 + rb + rl, u - rl * chunks, s_off[rl + 1] - b, [&](uint32_t q, uint32_t& j, float& x) {
+      sum_rows(c, [&](auto wide, uint32_t rl, uint32_t chunk) {
+        const uint32_t b = s_off[rl];
+        dec_sum_chunk<wide()>(a, r0 + rb + rl, chunk, s_off[rl + 1] - b, [&](uint32_t q, uint32_t& j, float& x) {
           const uint2 t = s_ent[s_ord[b + q]];
           j = __builtin_amdgcn_readfirstlane(t.x) & 16383u;
           x = __uint_as_float(__builtin_amdgcn_readfirstlane(t.y));
         });
-      }
+      });
     } else {
       // a single row
       for (uint32_t i = tid; i < nw; i += kDecBS) has[i] = 0;
@@ -964,11 +982,12 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
         word &= word - 1;
       }
       __syncthreads();
-      for (uint32_t u = w; u < chunks; u += NW)
-        dec_sum_chunk<VEC>(a, r0 + rb, u, tot, [&](uint32_t q, uint32_t& j, float& x) {
+      sum_rows(1u, [&](auto wide, uint32_t, uint32_t chunk) {
+        dec_sum_chunk<wide()>(a, r0 + rb, chunk, tot, [&](uint32_t q, uint32_t& j, float& x) {
           j = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(order[q]));
           x = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(dense[j])));
         });
+      });
     }
     rb += c;
   }
@@ -1114,7 +1133,7 @@ size_t sae_decode_workspace(uint32_t B, uint32_t K) {
 // cost counts steps of kDecStep entries, two a step of a chunk that does not
 // fit one.  Chunks of one step always, and the groups that the table then
 // leaves, took 36.2 ms for 4096 rows of 16384 latents with 4096 entries each
-// (two groups, which every workgroup read a dozen times), this 15.5 ms.
+// (two groups, which every workgroup read a dozen times), this 5.8 ms.
 struct DecSplit {
   uint32_t chunk, chunks, groups, group_rows, lanes_log2;
 };

@@ -202,6 +202,10 @@ def test_sae_decode(B, d_model, d_dict, k_row):
     (4096, 8, 512, "half"),           # sixteen rows a workgroup, more entries than it holds, long chunks
     (4100, 24, 600, "half"),          # the same, the last workgroup and chunk in part
     (24, 16, 16384, "half"),          # the largest count held at once, few workgroups
+    (3, 512, 3000, "half"),           # one row's columns over the waves
+    (250, 1992, 40, "half"),          # 31 and 1/8 pieces of 64 columns: read eight columns a lane
+    (250, 1984, 40, "half"),          # 31 pieces: a column a lane
+    (1000, 512, 4500, "some"),        # four rows a workgroup, together wide, taken in narrow runs where they are dense
 ])
 def test_decode_layouts(B, d_model, d_dict, kind):
     """Rows per workgroup, column remainders, workgroups per group, and rows
@@ -218,6 +222,9 @@ def test_decode_layouts(B, d_model, d_dict, kind):
         idx = np.concatenate([5 * d_dict + np.arange(d_dict), 400 * d_dict + np.arange(0, d_dict, 7)])
     elif kind == "half":
         idx = np.flatnonzero(g.random(B * d_dict) < 0.5)
+    elif kind == "some":
+        idx = np.concatenate([r * d_dict + g.permutation(d_dict)[:d_dict // 2 if r in (4, 5, 6, 7, 500, 501, 502) else 1]
+                              for r in range(B)])
     else:
         idx = np.concatenate([r * d_dict + np.arange(d_dict - 2) for r in {0, 1, B // 2, B - 1}])
     idx = g.permutation(idx).astype(np.int64)
@@ -265,9 +272,16 @@ def _decode_us(B, d_model, d_dict, k_row):
 def test_decode_time_follows_the_list():
     """A dense list (a quarter of every row) costs in proportion to its
     length: every workgroup reads its own rows' share of it, not the list.
-    Eight times the entries per row, of rows of eight columns, take about 50
+    Eight times the entries per row, of rows of eight columns, take about 36
     times as long (rows that no longer fit a workgroup together are taken in
     runs, each a pass over the share); with half the list read by every
     workgroup it was 121 times."""
     few, many = _decode_us(4096, 8, 16384, 512), _decode_us(4096, 8, 16384, 4096)
     assert many < 80 * few, (few, many)
+
+
+def test_decode_time_of_a_few_rows():
+    """Columns that a lane could read eight at a time are not left to one wave
+    (2.9 times the time of 510 columns, which are read one at a time)."""
+    wide, narrow = _decode_us(8, 512, 16384, 4096), _decode_us(8, 510, 16384, 4096)
+    assert wide < 2 * narrow, (wide, narrow)
