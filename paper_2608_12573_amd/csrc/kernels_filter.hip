@@ -149,8 +149,9 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
               .x;
     if (a.all_keys)
       for (uint32_t i = tid + kFiltBS; i < a.n_cut; i += kFiltBS) cutv = max(cutv, a.cut[i]);
-    if (a.all_keys && tau <= block_max<kFiltBS>(cutv, s_sc.wsum)) {
-      // some block may have dropped a key above tau: all sample keys
+    if (a.all_keys && tau < block_max<kFiltBS>(cutv, s_sc.wsum)) {
+      // some block may have dropped a key above tau (it is at most the block's
+      // cut key): all sample keys
       static_assert(kSelBins <= kLogBins, "histogram of the select");
       tau = block_select_kth<kFiltBS, kSelDigit>(
                 [&](auto f) {

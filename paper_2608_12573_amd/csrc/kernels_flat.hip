@@ -156,10 +156,12 @@ __global__ __launch_bounds__(kTauBS) void k_select_tau(TauArgs a) {
   // A union of at most 8*kTauBS keys is selected from registers; larger ones
   // by digit passes over LDS or memory.
   // Capped sample lists: the t-th largest of the union is the sample's
-  // unless a block that dropped keys has its cut key at or above it (every
-  // dropped key is at most its block's cut key), i.e. unless fewer than t
-  // union keys exceed the largest cut key; the select then takes all sample
-  // keys instead.
+  // unless a block that dropped keys has its cut key above it (every dropped
+  // key is at most its block's cut key, and one that only equals the t-th
+  // largest does not move it), i.e. unless fewer than t union keys reach the
+  // largest cut key; the select then takes all sample keys instead.  (With
+  // wide ties at tau the cut keys equal it; selecting again for those cost
+  // about 75 us in the filter, whose every block selects.)
   const uint32_t* keys = a.keys;
   uint32_t n = a.n;
   if (n <= static_cast<uint32_t>(kTauBS * E)) {
@@ -176,7 +178,7 @@ __global__ __launch_bounds__(kTauBS) void k_select_tau(TauArgs a) {
     const uint32_t kth = block_kth_regs<kTauBS, E, kSelDigit>(v, valid, min(n, static_cast<uint32_t>(kTauBS)), a.t, sel.hist, tlist,
                                                                  red, sel.scratch())
                              .x;
-    if (!a.cut || kth > block_max<kTauBS>(c, sel.wsum)) {
+    if (!a.cut || kth >= block_max<kTauBS>(c, sel.wsum)) {
       if (tid == 0) a.st->tau_key = kth;
       return;
     }
@@ -186,11 +188,11 @@ __global__ __launch_bounds__(kTauBS) void k_select_tau(TauArgs a) {
     uint32_t c = 0;
     for (uint32_t i = tid; i < a.n_cut; i += kTauBS) c = max(c, a.cut[i]);
     c = block_max<kTauBS>(c, sel.wsum);
-    uint32_t above = 0;
-    for_items<kTauBS, 8>(n, [&](uint32_t i) { return keys[i]; }, [&](uint32_t, uint32_t v) { above += v > c ? 1u : 0u; });
+    uint32_t reach = 0;
+    for_items<kTauBS, 8>(n, [&](uint32_t i) { return keys[i]; }, [&](uint32_t, uint32_t v) { reach += v >= c ? 1u : 0u; });
     // (the same in every thread: readfirstlane keeps the source uniform for
     // the compiler)
-    if (__builtin_amdgcn_readfirstlane(block_sum<kTauBS>(above, sel.wsum)) < a.t) {
+    if (__builtin_amdgcn_readfirstlane(block_sum<kTauBS>(reach, sel.wsum)) < a.t) {
       keys = a.all_keys;
       n = a.n_all;
     }

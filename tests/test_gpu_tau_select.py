@@ -15,7 +15,7 @@ import pytest
 import paper_2608_12573_amd as pk
 import workloads
 from oracle import keys as okeys, plan as oplan, profk as oprofk
-from gpu_util import check_rows, compare, gpu_f32, note, oracle_plan_of
+from gpu_util import check_rows, compare, gpu_f32, note, oracle_plan_of, plan_from_lib, torch
 
 pytestmark = pytest.mark.gpu
 
@@ -111,3 +111,62 @@ def test_vector_tau_small_capped_union(S, k, N, union):
     p = pk.plan(N, k, S_min=S, S_max=S, force_mode=pk.FORCE_FILTER)
     assert _capped_union(p) == union, (p.t, _capped_union(p))
     _check(_values("normal", N, S), k, 4, S_min=S, S_max=S, force_mode=pk.FORCE_FILTER)
+
+
+def _tied_top(N, share, seed):
+    """Uniform values, the largest `share` of them all 1."""
+    x = np.random.default_rng(seed).random(N, dtype=np.float32) * np.float32(0.5)
+    x[np.random.default_rng(seed + 1).random(N) < share] = 1.0
+    return x
+
+
+@pytest.mark.parametrize("N,k,S,share,M,union", [
+    (2**20, 458, 32768, 0.05, None, 512),        # every list full of ties: cut keys and tau all 1, an overflow
+    (2**20, 458, 32768, 0.05, 2**17, 512),       # ... in a buffer that holds them
+    (2**20, 458, 32768, 0.016, 2**17, 512),      # some lists full, others not
+    (2**22, 9000, 131072, 0.05, 2**18, 4096),    # the select launch, in registers
+    (2**22, 9000, 400000, 0.05, 2**18, 12512),   # ... by digit passes
+    (2**22, 9000, 400000, 0.0, 2**18, 12512),    # ... no ties, cut keys below tau
+])
+def test_vector_tau_equal_to_the_cut(N, k, S, share, M, union):
+    """Capped lists whose dropped keys only equal tau."""
+    p = pk.plan(N, k, S_min=S, S_max=S)
+    assert _capped_union(p) == union
+    if M:
+        p.M = M
+    x = _tied_top(N, share, N + k)
+    note(f"vec N={N} k={k} S={p.S} t={p.t} M={p.M} share={share}")
+    vals, idx, info = pk.topk(gpu_f32(x), k, seed=3, p=p)
+    ref = oprofk.run(okeys.f32_bits(x), "f32", k, plan_from_lib(p), 3)
+    assert (ref.tau_key == okeys.keys_of(np.array([0x3F800000], dtype=np.uint32), "f32")[0]) == (share > 0)
+    assert (ref.status == oprofk.STATUS_FILTERED) == bool(M)
+    compare(vals, idx, info, ref, "f32")
+
+
+def test_time_of_tau_equal_to_the_cut():
+    """Such a call selects from its lists: it takes a few us more than the
+    call that is given tau (with another select over the whole sample in
+    every filter workgroup it took about 75 us more)."""
+    t = torch()
+    N, k = 2**20, 458
+    p = pk.plan(N, k)
+    p.M = 2**17
+    x = gpu_f32(_tied_top(N, 0.05, 5))
+    ws = pk.workspace(p, pk.F32)
+    tau = int(okeys.keys_of(np.array([0x3F800000], dtype=np.uint32), "f32")[0])
+    note("time of topk and topk_tau on ties")
+    ev = [t.cuda.Event(enable_timing=True) for _ in range(2)]
+
+    def us(f):
+        best = float("inf")
+        for _ in range(6):
+            ev[0].record()
+            f()
+            ev[1].record()
+            t.cuda.synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) * 1e3)
+        return best
+
+    given, whole = us(lambda: pk.topk_tau(x, k, tau, p, ws=ws)), us(lambda: pk.topk(x, k, seed=3, p=p, ws=ws))
+    print(given, whole)
+    assert whole < given + 40, (given, whole)
