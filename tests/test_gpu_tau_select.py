@@ -54,6 +54,17 @@ def test_vector_tau(kind, N, k):
     _check(_values(kind, N, N % 1009 + k), k, 3)
 
 
+@pytest.mark.parametrize("kind", ["normal", "zeros", "packed", "wide"])
+@pytest.mark.parametrize("N,k,t", [(2**20, 1, 1), (2**20 + 5, 2, 4), (1374554, 3, 4), (300001, 2, 5), (300001, 4, 7),
+                                   (65983, 2, 8)])
+def test_vector_tau_few_ranks(kind, N, k, t):
+    """Unions of 32 lists of t keys, which one wave selects from, with the
+    candidate that has t keys found early, late or (ties) never."""
+    p = pk.plan(N, k)
+    assert (p.t, p.S) == (t, 32768)
+    _check(_values(kind, N, k), k, 6)
+
+
 @pytest.mark.parametrize("S,k", [(33, 1), (256, 3), (257, 8), (1025, 60), (2049, 200)])
 def test_vector_tau_small_samples(S, k):
     """Partial sample blocks down to one key above a block's size."""
