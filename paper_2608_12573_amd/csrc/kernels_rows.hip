@@ -39,6 +39,9 @@ template <int DT, int BS> constexpr uint32_t row_bins_per_thread() {
 // bits, whose histogram fits beside its other arrays.
 template <int DT, int BS> constexpr int row_block_digit() { return BS == kRowShortBS ? 8 : row_digit<DT>(); }
 
+// Largest t whose threshold 16-bit keys take by the maxima of lane groups.
+constexpr uint32_t kRowFewT = 32;
+
 struct RowArgs {
   const void* values;
   uint64_t row_stride;  // elements between row starts
@@ -136,8 +139,21 @@ __global__ __launch_bounds__(BS, BS == kRowShortBS ? 4 : 1) void k_rows(RowArgs 
         }
     }
     if (tid == 0) s_cnt = 0;
-    // 2. threshold
-    if (fast) {
+    // 2. threshold.  16-bit keys and t past a few: two radix passes of eight
+    // bits over the registers (2432 rows of 3510, t = 129: 30.5 us with the
+    // histogram of distances, 26.6; 5100 of 3734, t = 53: 43.2, 37.7; the samples
+    // kept in LDS took 28.1 and 40.9).  The one-wave kernel, whose registers
+    // are few and samples small, goes without the branch.
+    if (KB == 16 && BS != kRowShortBS && fast && a.t > kRowFewT) {
+      tau = block_select_kth<BS, kSelDigitRow>(
+                [&](auto f) {
+#pragma unroll
+                  for (int e = 0; e < 8; ++e)
+                    if ((valid >> e) & 1u) f(keys[e]);
+                },
+                a.t, KB, 0u, hist, scr)
+                .kth;
+    } else if (fast) {
       static_assert(kFastBucket * 8 >= kListWords * 4, "the list in comp");
       tau = block_kth_regs<BS, 8, kTauDigit>(keys, valid, min((a.S + 3) / 4, static_cast<uint32_t>(BS)), a.t, hist,
                                              reinterpret_cast<uint32_t*>(comp), s_red, scr)

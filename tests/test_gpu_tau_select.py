@@ -72,9 +72,11 @@ def test_vector_tau_small_samples(S, k):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("D,k,S", [(3001, 1, 64), (3001, 64, 300), (9001, 200, 2048), (9001, 200, 2049), (20001, 900, 4000)])
+@pytest.mark.parametrize("D,k,S", [(3001, 1, 64), (3001, 64, 300), (9001, 200, 2048), (9001, 200, 2049), (20001, 900, 4000),
+                                   (3001, 96, 366), (3001, 96, 378), (2001, 250, 257), (2001, 250, 500)])
 def test_row_tau(dtype, D, k, S):
-    """Samples in registers (up to 2048 draws on 256 threads) and in LDS."""
+    """Samples in registers (up to 2048 draws on 256 threads), with t on both
+    sides of 32, and in LDS."""
     x = np.concatenate([_values(kind, D, D + k) for kind in ("normal", "zeros", "packed")]).reshape(3, D)
     bits = okeys.f32_bits(x) if dtype == "f32" else workloads.f32_to_bf16_bits(
         np.where(np.isfinite(x), x, np.float32(0)))
