@@ -130,8 +130,8 @@ int profk_plan_rows(int64_t D, int64_t k, double eps, double recall, const profk
 
 size_t profk_workspace_size(const profk_plan_t* plan, int32_t dtype, int64_t batch) {
   if (!plan || !dtype_ok(dtype) || !plan_consistent(plan) || batch < 1) return 0;
-  // The one-workgroup row kernel keeps everything in LDS; rows outside its
-  // envelope run the vector kernels one row after another on one workspace.
+  // The row kernel keeps everything in LDS; rows outside its envelope run the
+  // vector kernels, at least one row at a time (profk_rows_workspace_size).
   if (batch > 1 && profk::rows_fit_block(*plan, dtype)) return 256;
   return profk::flat_layout(*plan, dtype, profk::device_cu_count()).bytes;
 }
@@ -269,32 +269,37 @@ int profk_topk_rows(const profk_plan_t* plan, int32_t dtype, const void* values,
   if (!small && ws_bytes < FL.bytes) return PROFK_EWORKSPACE;
   int64_t R = rows_at_once(FL, B, ws ? ws_bytes : 0);
   const int threads = profk::rows_block_threads(*plan, dtype, B, R, cus);
-  if (threads <= 0) {
-    // The vector path (sample, filter, refinement or fallback), R rows per
-    // launch on R workspaces, each row with its own Philox stream (counter
-    // word 1 = row); stream order lets the next R rows reuse them
-    // (launch_small needs no workspace and takes every row in one launch).
-    const uint64_t es = elem_size(dtype);
-    if (threads == profk::kRowsSmall) R = B;
-    (void)hipGetLastError();
-    for (int64_t r = 0; r < B; r += R) {
-      profk::FlatCall fc{plan, dtype, static_cast<const uint8_t*>(values) + static_cast<uint64_t>(r) * row_stride * es,
-                         static_cast<uint32_t>(D), static_cast<uint32_t>(k), seed, static_cast<uint64_t>(r),
-                         static_cast<uint8_t*>(out_vals) + static_cast<uint64_t>(r) * k * es, out_idx + r * k,
-                         static_cast<uint8_t*>(ws), FL, static_cast<hipStream_t>(stream),
-                         info_dev ? info_dev + r : nullptr, 0, 0};
-      fc.rows = static_cast<uint32_t>(B - r < R ? B - r : R);
+  // Rows of one launch: of the vector path (sample, filter, refinement or
+  // fallback) the R that the workspace holds, reused in stream order; of row
+  // blocks (launch_rows, and launch_small, which needs no workspace) what a
+  // grid takes.  Each row has its own Philox stream (counter word 1 = row).
+  const int64_t step = threads > 0 ? profk::rows_per_launch(threads)
+                       : threads == profk::kRowsSmall ? profk::rows_per_launch(profk::kSmallBS) : R;
+  const uint64_t es = elem_size(dtype);
+  (void)hipGetLastError();
+  for (int64_t r = 0; r < B; r += step) {
+    const uint32_t n = static_cast<uint32_t>(B - r < step ? B - r : step);
+    const void* const x = static_cast<const uint8_t*>(values) + static_cast<uint64_t>(r) * row_stride * es;
+    void* const v = static_cast<uint8_t*>(out_vals) + static_cast<uint64_t>(r) * k * es;
+    int64_t* const i = out_idx + r * k;
+    profk_info_t* const info = info_dev ? info_dev + r : nullptr;
+    hipError_t e;
+    if (threads > 0) {
+      const profk::RowCall c{plan, dtype, x, static_cast<uint32_t>(r), n, static_cast<uint32_t>(D),
+                             static_cast<uint32_t>(k), static_cast<uint64_t>(row_stride), seed, v, i,
+                             info, threads, static_cast<hipStream_t>(stream)};
+      e = profk::launch_rows(c);
+    } else {
+      profk::FlatCall fc{plan, dtype, x, static_cast<uint32_t>(D), static_cast<uint32_t>(k), seed,
+                         static_cast<uint64_t>(r), v, i, static_cast<uint8_t*>(ws), FL,
+                         static_cast<hipStream_t>(stream), info, 0, 0};
+      fc.rows = n;
       fc.stride = {static_cast<uint64_t>(row_stride) * es, FL.bytes};
-      const hipError_t e = profk::launch_flat(fc);
-      if (e != hipSuccess) return hip_fail(e);
+      e = profk::launch_flat(fc);
     }
-    return PROFK_OK;
+    if (e != hipSuccess) return hip_fail(e);
   }
-  profk::RowCall c{plan, dtype, values, static_cast<uint32_t>(B), static_cast<uint32_t>(D),
-                   static_cast<uint32_t>(k), static_cast<uint64_t>(row_stride), seed, out_vals, out_idx,
-                   info_dev, threads, static_cast<hipStream_t>(stream)};
-  const hipError_t e = profk::launch_rows(c);
-  return e == hipSuccess ? PROFK_OK : hip_fail(e);
+  return PROFK_OK;
 }
 
 int profk_debug_sample_indices(uint64_t seed, int64_t row, int64_t S, int64_t N, int64_t* out_dev,

@@ -44,6 +44,7 @@ constexpr uint32_t kRowFewT = 32;
 
 struct RowArgs {
   const void* values;
+  uint32_t row;         // of the batch: the first of this launch
   uint64_t row_stride;  // elements between row starts
   uint32_t D, k, k_req, S, t, M;
   int direct;
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(BS, BS == kRowShortBS ? 4 : 1) void k_rows(RowArgs 
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         const uint32_t blk = blk0 + q * BS + tid;
-        if (4 * blk < a.S) rnd[q] = philox4x64_10(blk, r, 0, 0, a.seed, 0);
+        if (4 * blk < a.S) rnd[q] = philox4x64_10(blk, a.row + r, 0, 0, a.seed, 0);
       }
       uint32_t raw[8];
 #pragma unroll
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(BS, BS == kRowShortBS ? 4 : 1) void k_rows(RowArgs 
       // the draws again (Philox words and gathers), for the tied draws' indices
       auto draws = [&](auto f) {
         for (uint32_t jb = tid; 4 * jb < a.S; jb += BS) {
-          const U64x4 rr = philox4x64_10(jb, r, 0, 0, a.seed, 0);
+          const U64x4 rr = philox4x64_10(jb, a.row + r, 0, 0, a.seed, 0);
           uint32_t raw[4], ix[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
@@ -426,7 +427,7 @@ int rows_block_threads(const profk_plan_t& p, int dtype, int64_t B, int64_t R, i
 template <int DT, int BS, bool PRE>
 static hipError_t launch_rows_t(const RowCall& c) {
   const profk_plan_t& p = *c.plan;
-  RowArgs ra{c.values, c.row_stride, c.D, c.k, static_cast<uint32_t>(p.k_req), static_cast<uint32_t>(p.S),
+  RowArgs ra{c.values, c.row, c.row_stride, c.D, c.k, static_cast<uint32_t>(p.k_req), static_cast<uint32_t>(p.S),
              static_cast<uint32_t>(p.t), static_cast<uint32_t>(p.M), p.mode == PROFK_MODE_DIRECT ? 1 : 0,
              c.seed, c.out_vals, c.out_idx, c.info, row_layout(p, c.dtype, BS)};
   const uint32_t lds = ra.L.bytes;

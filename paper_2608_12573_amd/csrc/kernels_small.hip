@@ -16,7 +16,6 @@
 
 namespace profk {
 
-constexpr int kSmallBS = 1024;
 constexpr int kSmallH = 8;            // 16-byte vectors per thread in each of two halves
 constexpr int kSmallU = 2 * kSmallH;
 constexpr uint32_t kSmallCap = 8192;  // elements collected in LDS

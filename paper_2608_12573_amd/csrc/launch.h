@@ -158,6 +158,7 @@ inline uint32_t filter_grid(const FlatCall& c) {
 
 hipError_t launch_flat(const FlatCall& c);
 // A vector selected without sampling that one workgroup holds in registers.
+constexpr int kSmallBS = 1024;                // its threads
 bool small_fits(int64_t n, int64_t k, int dtype);
 hipError_t launch_small(const FlatCall& c);
 // The filter pass of c into the workspace's candidate segments; tau from
@@ -226,6 +227,9 @@ bool rows_fit_block(const profk_plan_t& plan, int dtype);
 // R of them at a time (R = 0: no workspace for it), or kRowsSmall when each
 // row is selected without sampling by launch_small's workgroup.
 constexpr int kRowsSmall = -1;
+// Rows of one launch of row blocks: HIP refuses a grid of 2^32 threads, so a
+// larger batch takes several.
+constexpr int64_t rows_per_launch(int threads) { return (int64_t{1} << 31) / threads; }
 constexpr int64_t kRowSmallKb = 16;           // shortest row of a large batch it takes
 int rows_block_threads(const profk_plan_t& plan, int dtype, int64_t B, int64_t R, int num_cus);
 // Rows the vector path takes at a time when the workspace is its choice.
@@ -236,6 +240,7 @@ struct RowCall {
   const profk_plan_t* plan;
   int dtype;
   const void* values;
+  uint32_t row;         // Philox counter word 1 of the first row
   uint32_t B, D, k;
   uint64_t row_stride;
   uint64_t seed;

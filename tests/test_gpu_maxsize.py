@@ -123,3 +123,25 @@ def test_bf16_max_n_relu():
     rec = _check_exact(x, 4096, vals, idx, info)
     assert int(rec["status"]) == 0
     del x
+
+
+def test_rows_direct_past_one_grid():
+    # 2^22 + 5 rows of 16 KiB, each selected without sampling by 1024 threads:
+    # more threads than one launch takes.  Row r is zero but for one element
+    # (its place and value set by r), so the first two of each row are known.
+    th = torch()
+    B, D = (1 << 22) + 5, 8192
+    p = pk.plan_rows(D, 2, force_mode=pk.FORCE_DIRECT)
+    note(f"rows direct B={B} D={D} bf16")
+    x = th.zeros((B, D), device="cuda", dtype=th.bfloat16)
+    r = th.arange(B, device="cuda")
+    col = (r * 2654435761 + 12345) % D
+    val = (r % 128 + 1).to(th.bfloat16)
+    x[r, col] = val
+    vals, idx, info = pk.topk_rows(x, 2, p=p)
+    th.cuda.synchronize()
+    assert th.equal(idx[:, 0], col) and th.equal(vals[:, 0], val)
+    assert th.equal(idx[:, 1], (col == 0).to(th.int64)) and bool((vals[:, 1] == 0).all())
+    rec = pk.read_info(info)
+    assert np.all(rec["n_valid"] == 2) and np.all(rec["status"] == 3)
+    del x
