@@ -698,6 +698,7 @@ struct DecArgs {
   const uint16_t* w;   // W_dec [d_dict, d_model] bf16 bits
   const float* bias;   // b_dec [d_model]
   float* out;          // [B, d_model]
+  uint32_t block;      // first workgroup of this launch
   uint32_t rows;       // rows of a workgroup, at most kDecRows
   uint32_t groups;     // row groups, at most kDecMaxGroups
   uint32_t group_rows; // rows of a group, a multiple of `rows`
@@ -849,7 +850,7 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
   __shared__ uint32_t s_n;
   __shared__ uint32_t wsum[20];
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const uint32_t r0 = blockIdx.x * a.rows, nr = min(a.rows, a.B - r0);
+  const uint32_t r0 = (a.block + blockIdx.x) * a.rows, nr = min(a.rows, a.B - r0);
   const uint32_t nw = (a.d_dict + 31) / 32;
   const uint32_t group = r0 / a.group_rows;
   // visit(rb, nrows, f): f(e, o) for every entry e of rows [rb, rb + nrows),
@@ -1181,13 +1182,17 @@ hipError_t launch_sae_decode(const SaeDecodeCall& c) {
   const uint64_t table = static_cast<uint64_t>(c.B) * 3 + 2;
   const DecSplit sp = split_decode(c.B, c.K, rows, table, cus);
   DecArgs a{c.vals, c.idx, c.K, c.B, c.d_model, c.d_dict, static_cast<const uint16_t*>(c.w), c.bias, c.out,
-            rows, sp.groups, sp.group_rows, sp.chunk, sp.chunks, sp.lanes_log2, ws, ws + table};
+            0, rows, sp.groups, sp.group_rows, sp.chunk, sp.chunks, sp.lanes_log2, ws, ws + table};
   // (a single group is the list as it stands)
   if (a.groups > 1 && a.chunk == kDecStep) hipLaunchKernelGGL(k_dec_group<true>, dim3(a.chunks), dim3(kDecBS), 0, c.stream, a);
   else if (a.groups > 1) hipLaunchKernelGGL(k_dec_group<false>, dim3(a.chunks), dim3(kDecBS), 0, c.stream, a);
   const bool vec = c.d_model % 8 == 0 && reinterpret_cast<uintptr_t>(c.w) % 16 == 0;
-  if (vec) hipLaunchKernelGGL(k_dec_rows<true>, dim3(blocks), dim3(kDecBS), 0, c.stream, a);
-  else hipLaunchKernelGGL(k_dec_rows<false>, dim3(blocks), dim3(kDecBS), 0, c.stream, a);
+  constexpr uint32_t most = static_cast<uint32_t>(rows_per_launch(kDecBS));  // workgroups of a grid
+  for (; a.block < blocks; a.block += most) {
+    const dim3 G(blocks - a.block < most ? blocks - a.block : most);
+    if (vec) hipLaunchKernelGGL(k_dec_rows<true>, G, dim3(kDecBS), 0, c.stream, a);
+    else hipLaunchKernelGGL(k_dec_rows<false>, G, dim3(kDecBS), 0, c.stream, a);
+  }
   return hipGetLastError();
 }
 

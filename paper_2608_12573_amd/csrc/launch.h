@@ -227,8 +227,8 @@ bool rows_fit_block(const profk_plan_t& plan, int dtype);
 // R of them at a time (R = 0: no workspace for it), or kRowsSmall when each
 // row is selected without sampling by launch_small's workgroup.
 constexpr int kRowsSmall = -1;
-// Rows of one launch of row blocks: HIP refuses a grid of 2^32 threads, so a
-// larger batch takes several.
+// Workgroups (rows) of one launch: a grid of 2^32 threads does not run as asked,
+// so a larger batch takes several.
 constexpr int64_t rows_per_launch(int threads) { return (int64_t{1} << 31) / threads; }
 constexpr int64_t kRowSmallKb = 16;           // shortest row of a large batch it takes
 int rows_block_threads(const profk_plan_t& plan, int dtype, int64_t B, int64_t R, int num_cus);

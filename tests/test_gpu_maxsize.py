@@ -145,3 +145,22 @@ def test_rows_direct_past_one_grid():
     rec = pk.read_info(info)
     assert np.all(rec["n_valid"] == 2) and np.all(rec["status"] == 3)
     del x
+
+
+def test_decode_rows_past_one_grid():
+    # 16 rows a workgroup of 1024 threads: 2^26 rows are more than one launch
+    # takes.  Every 2^22nd row and the last ones have two latents.
+    th = torch()
+    B, d_dict, d = (1 << 26) + 33, 3, 8
+    note(f"decode B={B}")
+    rows = th.cat([th.arange(0, B, 1 << 22), th.tensor([B - 34, B - 32, B - 1])]).cuda()
+    idx = th.cat([rows * d_dict, rows * d_dict + 2])
+    vals = th.arange(idx.numel(), device="cuda", dtype=th.float32) + 1
+    w = (th.arange(d_dict * d, device="cuda").view(d_dict, d) + 1).to(th.bfloat16)
+    bias = th.arange(d, device="cuda", dtype=th.float32) * 100
+    out = pk.sae_decode(vals, idx, w, bias, B)
+    want = bias + vals[:rows.numel(), None] * w[0].float() + vals[rows.numel():, None] * w[2].float()
+    assert th.equal(out[rows], want)          # whole numbers below 2^24: exact in fp32
+    out[rows] = bias
+    for s in range(0, B, 1 << 24):
+        assert bool((out[s:s + (1 << 24)] == bias).all())
