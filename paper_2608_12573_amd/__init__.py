@@ -166,6 +166,7 @@ def plan_rows(D, k, eps=1e-6, recall=1.0, **kw):
 
 
 def workspace_size(p, dtype, batch=1):
+    """profk_workspace_size: the least workspace that a call accepts."""
     return int(lib().profk_workspace_size(ctypes.byref(p), dtype, batch))
 
 
@@ -211,9 +212,17 @@ def rows_workspace_size(p, dtype, B):
 
 def workspace(p, dtype, batch=1, device="cuda"):
     """A workspace for one vector, or (batch > 1) for topk_rows of that many
-    rows."""
+    rows: rows_workspace_size bytes, or workspace_size bytes, the least that it
+    accepts, where the device has no room for the former (at most 1 GiB)."""
     torch = _torch()
-    n = workspace_size(p, dtype, batch) if batch == 1 else rows_workspace_size(p, dtype, batch)
+    n = workspace_size(p, dtype, batch)
+    if batch > 1:
+        best = rows_workspace_size(p, dtype, batch)
+        if best > n:
+            try:
+                return torch.empty(best, dtype=torch.uint8, device=device)
+            except torch.OutOfMemoryError:
+                pass
     return torch.empty(max(n, 1), dtype=torch.uint8, device=device)
 
 

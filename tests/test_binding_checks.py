@@ -86,3 +86,23 @@ def test_sae_inputs():
     _raises(lambda: pk.sae_encode_dense(x, w, b), "CUDA tensor")
     _raises(lambda: pk.sae_decode(torch.zeros(8), torch.zeros(8, dtype=torch.int64), w, torch.zeros(64), 4),
             "CUDA tensor")
+
+
+@pytest.mark.parametrize("D,k,B", [(2**22, 32, 8), (2**20, 64, 5)])
+def test_rows_workspace_without_room_is_the_least(monkeypatch, D, k, B):
+    # a call that its least workspace satisfies does not fail for want of the
+    # larger one that it would be faster with
+    p = pk.plan_rows(D, k)
+    least, best = pk.workspace_size(p, pk.F32, B), pk.rows_workspace_size(p, pk.F32, B)
+    assert best == B * pk.workspace_size(p, pk.F32, 1) > least
+    assert pk.workspace(p, pk.F32, B, device="cpu").numel() == best
+    empty = torch.empty
+
+    def little_memory(n, **kw):
+        if n > least:
+            raise torch.OutOfMemoryError("no room")
+        return empty(n, **kw)
+
+    monkeypatch.setattr(torch, "empty", little_memory)
+    assert pk.workspace(p, pk.F32, B, device="cpu").numel() == least
+    assert pk._workspace_for(p, pk.F32, B, None, "cpu").numel() == least
