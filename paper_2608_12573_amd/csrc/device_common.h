@@ -302,9 +302,9 @@ __device__ __forceinline__ uint32_t lds_append(uint32_t* counter, bool take) {
 }
 
 // Wave 0 of a block (the caller makes only lanes of one wave call it)
-// finds the bin of `hist` (nb bins, a power of two, 16-byte aligned) that
-// holds rank krem (1-based) counted from the highest bin, and stores
-// sh.found = {bin, items in higher bins, items in the bin}.  Requires
+// finds the bin of `hist` (nb bins, a power of two up to 4096, 16-byte
+// aligned) that holds rank krem (1-based) counted from the highest bin, and
+// stores sh.found = {bin, items in higher bins, items in the bin}.  Requires
 // 1 <= krem <= the histogram's total.
 __device__ __forceinline__ void rank_bin_search(const uint32_t* hist, uint32_t nb, uint32_t krem,
                                                 SelectScratch& sh) {
@@ -371,7 +371,7 @@ template <int BS, int DIGIT, class Visit>
 __device__ __forceinline__ SelectResult block_select_kth(Visit visit, uint32_t kk, int nbits,
                                                          uint32_t prefix, uint32_t* hist,
                                                          SelectScratch& sh) {
-  static_assert(DIGIT >= 8 && DIGIT <= 13, "digit width");
+  static_assert(DIGIT >= 8 && DIGIT <= 12, "digit width");  // (rank_bin_search)
   const uint32_t tid = threadIdx.x;
   uint32_t krem = kk, above_total = 0, eq = 0;
   int hi = nbits;
@@ -546,6 +546,7 @@ __device__ __forceinline__ uint2 block_kth_regs(const uint32_t (&kv)[E], uint32_
                                                 SelectScratch& sc) {
   constexpr int NW = BS / kWave;
   constexpr uint32_t NB = 1u << DIGIT;
+  static_assert(DIGIT >= 8 && DIGIT <= 12, "digit width");  // (rank_bin_search)
   static_assert(2 * NW <= static_cast<int>(kKthGroups), "red");
   constexpr uint32_t NG = BS / kKthLanes;
   const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;

@@ -210,6 +210,7 @@ __device__ __forceinline__ void block_topk(const Src& src, uint32_t n, uint32_t 
 //                            (block-wide; may use sm.hist and sm.scratch).
 template <int BS, int DIGIT, class Src>
 __device__ __forceinline__ void window_topk(const Src& src, uint32_t kk, int keybits, const TopkSmem& sm) {
+  static_assert(DIGIT >= 8 && DIGIT <= 12, "digit width");  // (rank_bin_search)
   const uint32_t tid = threadIdx.x;
   const uint32_t cap = sm.cache_cap / 2;
   uint32_t* const pk = sm.cache;
