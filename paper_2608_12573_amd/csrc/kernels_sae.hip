@@ -840,11 +840,11 @@ template <bool VEC>
 __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
   constexpr int NW = kDecBS / kWave;
   // bitmaps and the words' prefix sums; dense rows: the row's latents in order
-  __shared__ uint32_t s_has[kDecRows * kDecWords];
-  __shared__ uint16_t s_pre[kDecRows * kDecWords];
+  __shared__ __align__(16) uint32_t s_has[kDecRows * kDecWords];
+  __shared__ __align__(16) uint16_t s_pre[kDecRows * kDecWords];
   // entries {row << 14 | latent, position and then value}, and their order;
   // dense rows: a value per latent
-  __shared__ uint2 s_ent[kDecCap];
+  __shared__ __align__(16) uint2 s_ent[kDecCap];
   __shared__ uint16_t s_ord[kDecCap];
   __shared__ uint32_t s_off[kDecRows + 1];
   __shared__ uint32_t s_n;
