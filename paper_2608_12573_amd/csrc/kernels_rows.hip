@@ -344,14 +344,14 @@ static inline uint32_t align16(uint32_t x) { return (x + 15u) & ~15u; }
 RowLayout row_layout(const profk_plan_t& p, int dtype, int bs) {
   RowLayout L;
   const uint32_t S = static_cast<uint32_t>(p.S), M = static_cast<uint32_t>(p.M);
-  const uint32_t k = static_cast<uint32_t>(p.k), t = static_cast<uint32_t>(p.t);
+  const uint32_t k = static_cast<uint32_t>(p.k);
   const bool f32 = dtype == PROFK_F32;
   const uint32_t ubs = static_cast<uint32_t>(bs);
   uint32_t P = 1;
   while (P < (k > ubs ? k : ubs)) P <<= 1;
   const uint32_t exch = 2u * P * 8u;
   const uint32_t b_bytes = align16(M * 4u);
-  const uint32_t samp_bytes = (row_fast_tau(S, bs) && t <= kCapListMax) ? 0u : S * 4u;   // samples kept in LDS
+  const uint32_t samp_bytes = row_fast_tau(S, bs) ? 0u : S * 4u;   // samples kept in LDS
   const uint32_t key_bytes = M * (f32 ? 4u : 2u);
   uint32_t a_bytes = align16(samp_bytes > key_bytes ? samp_bytes : key_bytes);
   if (a_bytes + b_bytes < exch) a_bytes = exch - b_bytes;
