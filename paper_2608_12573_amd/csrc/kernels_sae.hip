@@ -682,13 +682,17 @@ constexpr uint32_t kDecPer = 4;          // list entries per thread and step
 constexpr uint32_t kDecStep = kDecPer * kDecBS;
 constexpr uint32_t kDecMaxGroups = kDecBS;
 constexpr uint32_t kDecLanesLog2 = 4;    // fewest lanes that read a group's entries of one chunk
-// Fewest 64-column pieces of the rows in hand (two a wave) that are read eight
-// columns a lane.  With fewer pieces that left most waves without any: one
-// row of 512 columns was one wave's work (8 such rows with 4096 entries each
-// took 1284 us, 346 with a column a lane; 700 rows with 1024 entries 365 and 207).
-// At 32 pieces either is faster in places (1 row of 2048 columns with 512
-// entries: 93 us wide, 109 narrow; 1024 rows of 512 columns with 64: 35 and 27).
-constexpr uint32_t kDecWideMin = 32;
+// Most 64-column pieces of the rows in hand that are read a column a lane where
+// eight can be: one a wave, or two where the rows have kDecLong entries on
+// average.  Eight columns a lane leave most waves without any there: one row
+// of 512 columns is one wave's work (8 such rows with 4096 entries each take
+// 1284 us, 346 with a column a lane; 700 rows, 24 pieces, with 1024 entries 365
+// and 207, with 8 10.2 and 11.0; 1 row of 2048 columns, 32 pieces, with 512
+// entries 93 and 109).
+constexpr uint32_t kDecLong = 64;
+__host__ __device__ constexpr bool dec_narrow(uint32_t pieces, bool long_rows) {
+  return pieces <= kDecBS / kWave || (long_rows && pieces < 2 * kDecBS / kWave);
+}
 constexpr uint32_t kDecUngrouped = 16384;  // longest list that every workgroup reads whole
 
 struct DecArgs {
@@ -835,8 +839,9 @@ __device__ __forceinline__ void dec_sum_chunk(const DecArgs& a, uint32_t r, uint
 // row, with a flag and a value per latent in LDS (one workgroup of 256
 // threads per CU), took 146 us at that shape and grouping the list 24 us
 // before it; this takes 33 in all.
-// VEC: W_dec can be read eight columns a lane (dec_sum_chunk).
-template <bool VEC>
+// WIDE: rows of W_dec are read eight columns a lane (dec_sum_chunk), NARROW: one;
+// both: as the rows in hand ask for.
+template <bool WIDE, bool NARROW>
 __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
   constexpr int NW = kDecBS / kWave;
   // bitmaps and the words' prefix sums; dense rows: the row's latents in order
@@ -888,15 +893,21 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
       }
     }
   };
-  // sum_rows(nrows, f): f(wide, row, chunk of columns) for every chunk of nrows
-  // rows, a wave each
-  auto sum_rows = [&](uint32_t nrows, auto f) {
-    const uint32_t narrow = (a.d_model + kWave - 1) / kWave;
-    if (VEC && nrows * narrow >= kDecWideMin) {
-      const uint32_t chunks = (narrow + 7) / 8;
-      for (uint32_t u = w; u < nrows * chunks; u += NW) f(std::true_type{}, u / chunks, u % chunks);
-    } else {
-      for (uint32_t u = w; u < nrows * narrow; u += NW) f(std::false_type{}, u / narrow, u % narrow);
+  // sum_rows(nrows, n, f): f(wide, row, chunk of columns) for every chunk of
+  // nrows rows with n entries, a wave each
+  auto sum_rows = [&](uint32_t nrows, uint32_t n, auto f) {
+    const uint32_t pieces = (a.d_model + kWave - 1) / kWave;
+    if (WIDE && !(NARROW && dec_narrow(nrows * pieces, n >= nrows * kDecLong))) {
+      const uint32_t chunks = (pieces + 7) / 8;
+      for (uint32_t u = w; u < nrows * chunks; u += NW) {
+        const uint32_t rl = u / chunks;
+        f(std::true_type{}, rl, u - rl * chunks);
+      }
+    } else if (NARROW) {
+      for (uint32_t u = w; u < nrows * pieces; u += NW) {
+        const uint32_t rl = u / pieces;
+        f(std::false_type{}, rl, u - rl * pieces);
+      }
     }
   };
   static_assert(sizeof(s_ent) >= kDecMaxDict * 4 && sizeof(uint16_t) * kDecMaxDict <= sizeof(s_has), "a dense row");
@@ -958,7 +969,7 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
         s_ord[at] = static_cast<uint16_t>(p);
       }
       __syncthreads();
-      sum_rows(c, [&](auto wide, uint32_t rl, uint32_t chunk) {
+      sum_rows(c, n, [&](auto wide, uint32_t rl, uint32_t chunk) {
         const uint32_t b = s_off[rl];
         dec_sum_chunk<wide()>(a, r0 + rb + rl, chunk, s_off[rl + 1] - b, [&](uint32_t q, uint32_t& j, float& x) {
           const uint2 t = s_ent[s_ord[b + q]];
@@ -983,7 +994,7 @@ __global__ __launch_bounds__(kDecBS) void k_dec_rows(DecArgs a) {
         word &= word - 1;
       }
       __syncthreads();
-      sum_rows(1u, [&](auto wide, uint32_t, uint32_t chunk) {
+      sum_rows(1u, tot, [&](auto wide, uint32_t, uint32_t chunk) {
         dec_sum_chunk<wide()>(a, r0 + rb, chunk, tot, [&](uint32_t q, uint32_t& j, float& x) {
           j = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(order[q]));
           x = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(dense[j])));
@@ -1186,12 +1197,19 @@ hipError_t launch_sae_decode(const SaeDecodeCall& c) {
   // (a single group is the list as it stands)
   if (a.groups > 1 && a.chunk == kDecStep) hipLaunchKernelGGL(k_dec_group<true>, dim3(a.chunks), dim3(kDecBS), 0, c.stream, a);
   else if (a.groups > 1) hipLaunchKernelGGL(k_dec_group<false>, dim3(a.chunks), dim3(kDecBS), 0, c.stream, a);
+  // A workgroup's rows together are all narrow, or too many entries to be
+  // held at once, in runs of which some may be narrow, or wide (with a kernel
+  // of its own: the other variant's code costs it 0.3 us).
   const bool vec = c.d_model % 8 == 0 && reinterpret_cast<uintptr_t>(c.w) % 16 == 0;
+  const uint64_t per_row = c.K / c.B;
+  const bool narrow = !vec || dec_narrow(rows * cdiv_s(c.d_model, kWave), per_row >= kDecLong);
+  const bool runs = per_row * rows > kDecCap / 2;
   constexpr uint32_t most = static_cast<uint32_t>(rows_per_launch(kDecBS));  // workgroups of a grid
   for (; a.block < blocks; a.block += most) {
     const dim3 G(blocks - a.block < most ? blocks - a.block : most);
-    if (vec) hipLaunchKernelGGL(k_dec_rows<true>, G, dim3(kDecBS), 0, c.stream, a);
-    else hipLaunchKernelGGL(k_dec_rows<false>, G, dim3(kDecBS), 0, c.stream, a);
+    if (narrow) hipLaunchKernelGGL((k_dec_rows<false, true>), G, dim3(kDecBS), 0, c.stream, a);
+    else if (runs) hipLaunchKernelGGL((k_dec_rows<true, true>), G, dim3(kDecBS), 0, c.stream, a);
+    else hipLaunchKernelGGL((k_dec_rows<true, false>), G, dim3(kDecBS), 0, c.stream, a);
   }
   return hipGetLastError();
 }

@@ -203,9 +203,11 @@ def test_sae_decode(B, d_model, d_dict, k_row):
     (4100, 24, 600, "half"),          # the same, the last workgroup and chunk in part
     (24, 16, 16384, "half"),          # the largest count held at once, few workgroups
     (3, 512, 3000, "half"),           # one row's columns over the waves
-    (250, 1992, 40, "half"),          # 31 and 1/8 pieces of 64 columns: read eight columns a lane
-    (250, 1984, 40, "half"),          # 31 pieces: a column a lane
-    (1000, 512, 4500, "some"),        # four rows a workgroup, together wide, taken in narrow runs where they are dense
+    (250, 1024, 40, "half"),          # 16 pieces of 64 columns: a column a lane
+    (250, 1032, 40, "half"),          # 17 pieces: eight columns a lane
+    (250, 1984, 150, "half"),         # 31 pieces and more than 64 entries a row: a column a lane
+    (250, 1992, 150, "half"),         # 32 pieces: eight columns a lane
+    (1000, 512, 4500, "some"),        # a few dense rows, taken in runs, eight columns a lane
 ])
 def test_decode_layouts(B, d_model, d_dict, kind):
     """Rows per workgroup, column remainders, workgroups per group, and rows
@@ -244,6 +246,31 @@ def test_decode_layouts(B, d_model, d_dict, kind):
     np.add.at(mag, r, np.abs(v[:, None] * w[j]))
     terms = np.bincount(r, minlength=B)[:, None]
     assert np.all(np.abs(out - ref) <= (terms + 2) * 2.0**-24 * mag)
+
+
+@pytest.mark.parametrize("B,d_model,d_dict,share", [
+    (1000, 512, 2200, 0.5),     # four rows a workgroup, held at once, eight columns a lane
+    (1000, 512, 4500, 0.5),     # runs of two rows, a column a lane
+    (258, 1024, 9000, 0.5),     # two rows a workgroup, runs of one
+    (4096, 192, 1200, 0.5),     # sixteen rows a workgroup, runs of eight
+    (4096, 256, 1100, 0.5),     # the same, eight columns a lane
+    (300, 512, 16384, 0.9),     # rows that are not held at once
+])
+def test_decode_dense_rows(B, d_model, d_dict, share):
+    """Long rows in every workgroup, against a matrix product in fp64, with the
+    bound of test_decode_layouts."""
+    t = torch()
+    g = np.random.default_rng(B + d_dict)
+    z = np.where(g.random((B, d_dict)) < share, g.standard_normal((B, d_dict)), 0).astype(np.float32)
+    idx = g.permutation(np.flatnonzero(z))
+    wb = workloads.f32_to_bf16_bits(g.standard_normal((d_dict, d_model)).astype(np.float32))
+    bias = g.standard_normal(d_model).astype(np.float32)
+    note(f"decode dense B={B} d_model={d_model} d_dict={d_dict} K={idx.size}")
+    out = pk.sae_decode(t.from_numpy(z.reshape(-1)[idx]).cuda(), t.from_numpy(idx).cuda(),
+                        gpu_bf16(wb).view(d_dict, d_model), t.from_numpy(bias).cuda(), B).cpu().numpy()
+    w, z = (wb.astype(np.uint32) << 16).view(np.float32).reshape(d_dict, d_model).astype(np.float64), z.astype(np.float64)
+    terms = (z != 0).sum(axis=1)[:, None]
+    assert np.all(np.abs(out - (z @ w + bias)) <= (terms + 2) * 2.0**-24 * (np.abs(z) @ np.abs(w) + np.abs(bias)))
 
 
 def _decode_us(B, d_model, d_dict, k_row):
