@@ -395,6 +395,11 @@ bool rows_fit_block(const profk_plan_t& p, int dtype) {
 // more than the row (256 / 64 threads: 8192 rows of 16 KB 72 / 61, of 4 KB
 // 70 / 34; 512 of 16 KB 17 / 19).  The lexicographic rule does not fit its
 // registers.
+// Under the lexicographic rule, whose blocks have more steps after the stream,
+// small workgroups stay ahead for long rows too, while there are enough for
+// several on each CU and four fit its LDS (256 / 512 threads, bf16: 4096 rows of
+// 256 KB 231 / 281, 1214 of 162 KB 65 / 74; fp32: 1024 of 400 KB 94 / 100; but 512
+// of 256 KB 55 / 49, and 1000 fp32 of 256 KB with k = 1000, 54 KB of LDS, 161 / 112).
 // The vector path (sample, filter, refinement: three launches of which each
 // takes R rows) shares every row out over the chip, which pays where a row is
 // long and the rows are few.  Measured (us, 1024 threads / vector path, k = 32
@@ -420,7 +425,8 @@ int rows_block_threads(const profk_plan_t& p, int dtype, int64_t B, int64_t R, i
       !p.lexicographic && p.k <= kRowShortBS * 4 && p.S <= kRowShortBS * 8 && p.M <= kRowShortM)
     return kRowShortBS;
   if (kb >= 32 && B <= num_cus && wide) return kRowWideBS;
-  if (kb >= 128 && fits(kRowMidBS)) return kRowMidBS;
+  const bool many = B > 2 * num_cus && row_layout(p, dtype, kRowBS).bytes <= 39 * 1024;  // (and 0.5 KB static)
+  if (kb >= 128 && fits(kRowMidBS) && !(p.lexicographic && many)) return kRowMidBS;
   return kRowBS;
 }
 

@@ -99,3 +99,13 @@ def test_row_block_one_wave(dtype, D, k, offset, extra):
     assert p.mode == pk.MODE_FILTER and p.S <= 512 and p.M <= 1024
     st = check_rows(b, dtype, k, p, oracle_plan_of(p, rows=True), 1, offset=offset, stride=D + extra)
     assert st.count(oprofk.STATUS_FILTERED) >= B - 3 and oprofk.STATUS_OVERFLOW in st
+
+
+@pytest.mark.parametrize("B", [512, 513])
+def test_row_block_lexicographic_long_rows(B):
+    """More than two long rows per compute unit go to the smaller workgroup."""
+    D, k = 65543, 20
+    p = pk.plan_rows(D, k, lexicographic=1)
+    opts = dataclasses.replace(oplan.ROW_OPTS, lexicographic=True)
+    st = check_rows(_bits("bf16", B, D, seed=B), "bf16", k, p, oracle_plan_of(p, opts=opts), 4, offset=1)
+    assert st == [oprofk.STATUS_FILTERED] * B
