@@ -677,28 +677,28 @@ __device__ __forceinline__ uint32_t wave_kth(const uint32_t (&kv)[E], uint32_t v
     mx = max(mx, in ? kv[e] : 0u);
     nmn = max(nmn, in ? ~kv[e] : 0u);
   }
-  mx = wave_max_u32(mx);
-  if (kk == 1) return mx;
-  const uint32_t mn = ~wave_max_u32(nmn);
+  // (scalars, and the loop's result taken after it: the loop then runs on the
+  // scalar unit but for its compares)
+  const uint32_t top = __builtin_amdgcn_readfirstlane(wave_max_u32(mx));
+  const uint32_t mn = ~__builtin_amdgcn_readfirstlane(wave_max_u32(nmn));
+  if (kk == 1 || top == mn) return top;
   uint32_t d[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) d[e] = ((valid >> e) & 1u) ? kv[e] - mn : 0u;  // (0 is never counted)
-  uint32_t res = 0;
-  for (int bit = mx == mn ? -1 : 31 - __clz(mx - mn); bit >= 0; --bit) {
-    const uint32_t cand = res | (1u << bit);
-    uint32_t n = 0;
+  uint32_t res = 0, cand = 0, n = 0;
+  for (int bit = 31 - __clz(top - mn); bit >= 0; --bit) {
+    cand = res | (1u << bit);
+    n = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) n += static_cast<uint32_t>(__popcll(__ballot(d[e] >= cand)));
-    if (n == kk) {
-      uint32_t low = 0xFFFFFFFFu;
-#pragma unroll
-      for (int e = 0; e < E; ++e) low = min(low, d[e] >= cand ? d[e] : 0xFFFFFFFFu);
-      res = ~wave_max_u32(~low);
-      break;
-    }
+    if (n == kk) break;
     if (n > kk) res = cand;
   }
-  return mn + res;
+  if (n != kk) return mn + res;
+  uint32_t low = 0xFFFFFFFFu;
+#pragma unroll
+  for (int e = 0; e < E; ++e) low = min(low, d[e] >= cand ? d[e] : 0xFFFFFFFFu);
+  return mn + ~wave_max_u32(~low);
 }
 
 // Number of leading bits shared by every value in [lo, hi] (lo <= hi),

@@ -29,6 +29,13 @@ struct FilterArgs {
   CallState* st;
   const uint32_t* union_keys;  // sample union to select tau from, or null: tau in st
   uint32_t union_n, t;
+  // One wave selects tau from a small union, of which every wave then holds a
+  // copy.  Capped lists (all_keys) are selected by the whole block, each key
+  // held once, since every thread takes part in the check of the cut keys.
+  // (A flag from the host: with the condition formed here, the compiler moved
+  // the select behind the other branches and had it wait for the first step's
+  // loads, 0.5 to 1.2 us.)
+  uint32_t one_wave;
   // capped sample lists: the n_cut blocks' cut keys and all n_all sample
   // keys, as in k_select_tau; otherwise all_keys is null and cut any
   // readable word (n_cut = 1)
@@ -92,17 +99,13 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
   const uint32_t vend = a.nvec;
   const uint32_t vstride = gridDim.x * kTile;
   constexpr int E = kFiltTauMax / kFiltBS;
-  // One wave selects tau from a small union, of which every wave then holds a
-  // copy.  Capped lists (all_keys) are selected by the whole block, each key
-  // held once, since every thread takes part in the check of the cut keys.
-  const bool one_wave = !a.all_keys && a.union_n <= kFiltTauWave * kWave;
   uint32_t uk[E];
   uint32_t valid = 0, cutv = 0;
   if (a.union_n) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       // one wave: lane + 64 e (every wave holds them); else tid + 256 e
-      const uint32_t i = one_wave ? lane + kWave * e : tid + kFiltBS * e;
+      const uint32_t i = a.one_wave ? lane + kWave * e : tid + kFiltBS * e;
       uk[e] = a.union_keys[min(i, a.union_n - 1)];
       if (i < a.union_n) valid |= 1u << e;
     }
@@ -130,7 +133,7 @@ __global__ __launch_bounds__(kFiltBS) void k_filter(FilterArgs a) {
 
   // ---- threshold (stage 2) when the sample union is small
   uint32_t tau;
-  if (a.union_n > 0 && one_wave) {
+  if (a.one_wave) {
     if (tid < kWave) {
       uint32_t few[kFiltTauWave];
 #pragma unroll
@@ -320,6 +323,7 @@ static hipError_t launch_filter_t(const FlatCall& c, CallState* st, const uint32
   const uint32_t nvec = (c.n - head) / EPV;
   FilterArgs fa{c.values, c.n, head, nvec, L.seg_cap, st,
                 union_keys, union_keys ? L.union_n : 0u, static_cast<uint32_t>(c.plan->t),
+                union_keys && !L.cap_list && L.union_n <= kFiltTauWave * kWave ? 1u : 0u,
                 L.cap_list ? at<uint32_t>(c.ws, L.off_cut) : union_keys, L.cap_list ? L.G_s : 1u,
                 union_keys && L.cap_list ? at<uint32_t>(c.ws, L.off_all_keys) : nullptr,
                 static_cast<uint32_t>(c.plan->S),
