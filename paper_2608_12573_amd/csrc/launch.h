@@ -39,8 +39,8 @@ constexpr uint32_t kCapListMax = 32;          // longest capped list; smaller t 
 // S), each block keeps only its top c (c = 16 or 32, at least mu + 8
 // sqrt(mu) + 2) and its c-th largest key, and the blocks store every key.
 // The t-th largest of the union of the lists is the sample's t-th largest
-// whenever no block that dropped keys has its c-th key at or above it;
-// otherwise tau is selected again from all S keys.
+// whenever no block that dropped keys has its c-th key above it; otherwise
+// tau is selected again from all S keys.
 constexpr uint32_t kCapListSmall = 16;
 constexpr int kTauBS = 1024;
 constexpr int kFiltBS = 256;                  // threads of a filter block
