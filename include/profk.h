@@ -193,7 +193,8 @@ int profk_topk_simple(const float* values, int64_t N, int64_t k, uint64_t seed,
  *   Rows run in one workgroup each, entirely in LDS, or, where a row is long
  *   and the rows are few or the buffer exceeds the LDS, on the vector path of
  *   profk_topk, as many at a time as `ws` holds a vector workspace for, with
- *   the same per-row sample stream and result. */
+ *   the same per-row sample stream and result.  Where no workspace is needed,
+ *   one that is not 16-byte aligned is left alone. */
 int profk_topk_rows(const profk_plan_t* row_plan, int32_t dtype,
                     const void* values, int64_t B, int64_t D,
                     int64_t row_stride, int64_t k, uint64_t seed,

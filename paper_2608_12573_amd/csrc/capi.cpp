@@ -267,7 +267,10 @@ int profk_topk_rows(const profk_plan_t* plan, int32_t dtype, const void* values,
   const bool small = profk::rows_fit_block(*plan, dtype);
   if (!small && !ws) return PROFK_ENULL;
   if (!small && ws_bytes < FL.bytes) return PROFK_EWORKSPACE;
-  int64_t R = rows_at_once(FL, B, ws ? ws_bytes : 0);
+  // A workspace that is not needed is used where the vector path can: its
+  // regions take 32-bit atomics and 16-byte loads, which want them aligned.
+  const bool usable = ws && (!small || reinterpret_cast<uintptr_t>(ws) % 16 == 0);
+  const int64_t R = rows_at_once(FL, B, usable ? ws_bytes : 0);
   const int threads = profk::rows_block_threads(*plan, dtype, B, R, cus);
   // Rows of one launch: of the vector path (sample, filter, refinement or
   // fallback) the R that the workspace holds, reused in stream order; of row

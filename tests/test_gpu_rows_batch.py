@@ -85,3 +85,23 @@ def test_workspace_sizes_agree(D, k):
         if ref is None:
             ref = got
         assert all(np.array_equal(a, b) for a, b in zip(ref, got)), n
+
+
+@pytest.mark.parametrize("shift", [0, 1, 4, 8, 16])
+def test_unaligned_workspace(shift):
+    """A plan that needs no workspace accepts one at any address: the vector
+    path takes it where it is 16-byte aligned, else it is left as it is."""
+    t = torch()
+    B, D, k = 4, 2**20, 64
+    p = pk.plan_rows(D, k)
+    assert _batched(p, "f32", B) and pk.workspace_size(p, pk.F32, B) == 256
+    x = gpu_f32(workloads.normal_f32(B * D, seed=13)).view(B, D)
+    n = pk.rows_workspace_size(p, pk.F32, B)
+    buf = t.full((n + 64,), 0xA5, dtype=t.uint8, device="cuda")
+    assert buf.data_ptr() % 256 == 0
+    note(f"rows B={B} D={D} k={k} workspace at {shift}")
+    got = [a.view(-1) for a in pk.topk_rows(x, k, p=p, ws=buf[shift:shift + n], seed=2)]
+    ref = [a.view(-1) for a in pk.topk_rows(x, k, p=p, seed=2)]
+    assert all(t.equal(a, b) for a, b in zip(got, ref))
+    assert bool((buf == 0xA5).all()) == (shift % 16 != 0)
+    assert bool((buf[:shift] == 0xA5).all()) and bool((buf[shift + n:] == 0xA5).all())
