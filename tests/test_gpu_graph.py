@@ -127,3 +127,63 @@ def test_graph_sae_encode_topk():
     call()
     assert int(pk.read_info(info)[0]["status"]) == 0
     _replays_equal_eager(call, [out[0], out[1], info])
+
+
+@pytest.mark.parametrize("kw", [{}, dict(lexicographic=1)])
+def test_graph_rows_batched(kw):
+    # long rows on the batched vector path, in two launches of each kernel;
+    # one of constant values, which the key rule overflows on (its fallback's
+    # tickets start over on every replay)
+    t = torch()
+    B, D, k = 4, 2**20 + 3, 64
+    x = workloads.normal_f32(B * D, seed=8).reshape(B, D)
+    x[2] = 1.5
+    p = pk.plan_rows(D, k, **kw)
+    one = pk.workspace_size(p, pk.F32, 1)
+    assert pk.rows_workspace_size(p, pk.F32, B) == B * one
+    note(f"graph rows batched B={B} D={D} k={k} {kw}")
+    g = gpu_f32(x.reshape(-1)).view(B, D)
+    ws = t.empty(3 * one, dtype=t.uint8, device="cuda")
+    out = (t.empty(B * k, dtype=t.float32, device="cuda"), t.empty(B * k, dtype=t.int64, device="cuda"))
+    info = t.empty(B * pk.INFO_BYTES, dtype=t.uint8, device="cuda")
+    call = lambda: pk.topk_rows(g, k, seed=0, p=p, ws=ws, out=out, info=info)
+    call()
+    status = [int(s) for s in pk.read_info(info)["status"]]
+    assert status == [oprofk.STATUS_FILTERED] * 2 + [oprofk.STATUS_FILTERED if kw else oprofk.STATUS_OVERFLOW] + \
+        [oprofk.STATUS_FILTERED]
+    assert t.equal(out[1].view(B, k)[2], t.arange(k, device="cuda"))
+    _replays_equal_eager(call, [out[0], out[1], info])
+
+
+def test_graph_small_vector():
+    t = torch()
+    g = gpu_f32(workloads.normal_f32(50001, seed=9))
+    p = pk.plan(50001, 100)
+    assert p.mode == pk.MODE_DIRECT
+    note("graph small N=50001 k=100")
+    ws = pk.workspace(p, pk.F32)
+    out = (t.empty(100, dtype=t.float32, device="cuda"), t.empty(100, dtype=t.int64, device="cuda"))
+    info = t.empty(pk.INFO_BYTES, dtype=t.uint8, device="cuda")
+    call = lambda: pk.topk(g, 100, p=p, ws=ws, out=out, info=info)
+    call()
+    assert t.equal(out[0], t.topk(g, 100).values)
+    _replays_equal_eager(call, [out[0], out[1], info])
+
+
+@pytest.mark.parametrize("B,d_model,d_dict,k_row", [(1024, 128, 2048, 32), (256, 64, 4096, 2000)])
+def test_graph_sae_decode(B, d_model, d_dict, k_row):
+    # the list sorted by row group in chunks of one step, and of several
+    t = torch()
+    gen = t.Generator(device="cuda").manual_seed(31)
+    idx = t.rand((B, d_dict), generator=gen, device="cuda").argsort(dim=1)[:, :k_row]
+    idx = (idx + t.arange(B, device="cuda")[:, None] * d_dict).reshape(-1)
+    idx = idx[t.randperm(idx.numel(), generator=gen, device="cuda")].contiguous()
+    vals = t.rand(idx.numel(), generator=gen, device="cuda")
+    w = t.randn((d_dict, d_model), generator=gen, device="cuda").to(t.bfloat16)
+    b = t.randn(d_model, generator=gen, device="cuda")
+    note(f"graph decode B={B} d_model={d_model} d_dict={d_dict} k_row={k_row}")
+    ws = t.empty(pk.lib().profk_sae_decode_workspace_size(B, idx.numel()), dtype=t.uint8, device="cuda")
+    out = t.empty((B, d_model), dtype=t.float32, device="cuda")
+    call = lambda: pk.sae_decode(vals, idx, w, b, B, out=out, ws=ws)
+    call()
+    _replays_equal_eager(call, [out])
